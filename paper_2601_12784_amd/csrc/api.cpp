@@ -50,6 +50,7 @@ CombineArgs combine_args(const sf_attn_desc* desc, const sf_plan_info* info, con
   CombineArgs a = {};
   a.items = rows ? rows : work_dev + (table_rows(info->num_workers) + info->num_work) * kItemInts;
   a.num_items = info->num_combine;
+  a.num_partials = info->num_partials;
   a.part_o = info->num_partials ? ws.part_o : nullptr;
   a.part_lse = info->num_partials ? ws.part_lse : nullptr;
   a.out = out;

@@ -84,6 +84,7 @@ struct RowCopy {
 struct CombineArgs {
   const int32_t* items;       // merge rows
   int32_t num_items;
+  int32_t num_partials;       // segments of all of them
   const float* part_o;
   const float* part_lse;
   float* out;
