@@ -864,73 +864,112 @@ __global__ __launch_bounds__(64 * kWG) __attribute__((amdgpu_waves_per_eu(2, 2))
 // ---------------------------------------------------------------------------
 // per-page fp8 quantizer
 // ---------------------------------------------------------------------------
-// One block per listed page: for every KV head, the K tile and then the V
-// tile (16 * D bf16 values each) become E4M3 codes with one scale per tile:
+// For every listed page and KV head, the K tile and the V tile (16 * D bf16
+// values each) become E4M3 codes with one scale per tile:
 //   amax = max |x| over the valid slots;  scale = amax / 448, inv = 448 / amax
 //   (correctly rounded; 1 and 1 for an all-zero tile);
 //   code = round-to-nearest-even(x * inv), 0 for slots past the valid count.
+// One wave per tile, the tile in registers (D / 4 values per lane): read once,
+// no LDS and no barrier, so a list of any length is 2 * Hkv independent waves
+// per page. Lane l loads exactly the values whose codes make its own 16-byte
+// pieces of the fp8 layouts: of a K tile the pieces l and l + 64 (dims d and
+// d + 32 of one slot) of each 64 dims, of a V tile slots 4 * (l / 16) .. + 3 of
+// dims l % 16 + 16 * f; every wave access is contiguous over the instruction.
+// Bound by memory: the long-tail cache (44152 pages, 1.45 GB in, 0.72 GB out)
+// takes 420 us = 5.2 TB/s, more than a 4 GiB device copy's 4.8 (one block per
+// page reading each tile twice, with two barriers: 465 us). Nontemporal
+// stores are worth 5 % of it (the codes are not read again soon), a page's K
+// tiles before its V tiles 0.5 %; fewer, longer-lived waves (2048 workgroups)
+// take 430 us, cached loads 429.
+__device__ __forceinline__ float bf16_word(const uint32_t* w, int e) {
+  return e & 1 ? __builtin_bit_cast(float, w[e >> 1] & 0xFFFF0000u) : __builtin_bit_cast(float, w[e >> 1] << 16);
+}
+
+constexpr int kQuantWaves = 4;                  // tiles (waves) per workgroup
+constexpr int64_t kQuantMaxBlocks = 1 << 22;    // beyond it the waves take several tiles each
+
 template <int D>
-__global__ __launch_bounds__(256) void quantize_fp8_kernel(QuantArgs a) {
-  __shared__ float red[4];
-  const int page = as_constant(a.pages)[blockIdx.x];
-  const int valid = as_constant(a.valid)[blockIdx.x];
-  constexpr int kPieces = kPage * D / 8;   // 8 values per piece
-  for (int kvh = 0; kvh < a.num_kv_heads; ++kvh) {
+__global__ __launch_bounds__(64 * kQuantWaves) void quantize_fp8_kernel(QuantArgs a) {
+  constexpr int kPieces = D / 64;   // 16-byte code pieces per lane
+  const int lane = lane_id();
+  const int col = lane & 15;
+  const int grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int64_t tiles = int64_t(a.num_pages) * a.num_kv_heads * 2;
+  for (int64_t t = int64_t(blockIdx.x) * kQuantWaves + wave; t < tiles; t += int64_t(gridDim.x) * kQuantWaves) {
+    const int idx = int(t / (2 * a.num_kv_heads));
+    const int rem = int(t - int64_t(idx) * 2 * a.num_kv_heads);
+    const bool is_v = rem >= a.num_kv_heads;
+    const int kvh = is_v ? rem - a.num_kv_heads : rem;
+    const int page = as_constant(a.pages)[idx];
+    const int valid = as_constant(a.valid)[idx];
+    const size_t tile = tile_offset(page, a.num_kv_heads, kvh, D);
+    // x[p][0..7]: 16 values as bf16 pairs, in the order of their codes
+    uint32_t x[kPieces][8];
+    if (is_v) {
+      const uint16_t* src = a.v_src + tile + v_elem(4 * grp, col);
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      const uint16_t* src = (which == 0 ? a.k_src : a.v_src) + tile_offset(page, a.num_kv_heads, kvh, D);
-      uint8_t* dst = (which == 0 ? a.k_dst : a.v_dst) + tile_offset(page, a.num_kv_heads, kvh, D);
-      float* scale_out = which == 0 ? a.k_scale : a.v_scale;
-      // Slot of value e of piece i: K tiles hold 8 dims of one slot per
-      // piece; V tiles 8 consecutive slots of one dim.
-      auto slot_of = [&](int piece, int e) { return which == 0 ? piece % kPage : (piece * 8 + e) % kPage; };
-      float amax = 0.f;
-      for (int i = threadIdx.x; i < kPieces; i += 256) {
-        const u32x4 x = load16(src + 8 * i);
+      for (int p = 0; p < kPieces; ++p)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float v = bf16_value((x[e / 2] >> (16 * (e & 1))) & 0xFFFFu);
-          if (slot_of(i, e) < valid) amax = fmaxf(amax, fabsf(v));
+        for (int f = 0; f < 4; ++f) {
+          const u32x2 w = stream8(src + v_elem(0, 64 * p + 16 * f));
+          x[p][2 * f] = w[0];
+          x[p][2 * f + 1] = w[1];
         }
-      }
+    } else {
+      const uint16_t* src = a.k_src + tile + 8 * lane;
 #pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
-      __syncthreads();
-      amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-      __syncthreads();
-      const float inv = amax > 0.f ? __fdiv_rn(448.f, amax) : 1.f;
-      if (threadIdx.x == 0) scale_out[size_t(page) * a.num_kv_heads + kvh] = amax > 0.f ? __fdiv_rn(amax, 448.f) : 1.f;
-      for (int i = threadIdx.x; i < kPieces; i += 256) {
-        const u32x4 x = load16(src + 8 * i);
-        uint32_t w[2];
+      for (int p = 0; p < kPieces; ++p)
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          float f[4];
+        for (int h = 0; h < 2; ++h) {
+          const u32x4 w = stream16(src + k_elem(0, 64 * p + 32 * h, D));
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int idx = 4 * q + e;
-            const float v = bf16_value((x[idx / 2] >> (16 * (idx & 1))) & 0xFFFFu);
-            f[e] = slot_of(i, idx) < valid ? v * inv : 0.f;
-          }
-          int packed = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], 0, false);
-          packed = __builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], packed, true);
-          w[q] = uint32_t(packed);
+          for (int i = 0; i < 4; ++i) x[p][4 * h + i] = w[i];
         }
-        if (which == 0) {
-          // K piece i: dims d0 .. d0 + 7 of slot t, contiguous in the fp8 layout
-          const int t = i % kPage, d0 = 8 * (i / kPage);
-          const int off = (((d0 / 64) * 4 + (d0 % 32) / 8) * kPage + t) * 16 + ((d0 / 32) % 2) * 8;
-          *reinterpret_cast<u32x2*>(dst + off) = u32x2{w[0], w[1]};
-        } else {
-          // V piece i: slots t0 .. t0 + 7 of dim d, two runs of four slots
-          const int d = i / 2, t0 = 8 * (i % 2);
-          const int off = (((d / 64) * 4 + t0 / 4) * kPage + d % 16) * 16 + ((d / 16) % 4) * 4;
-          *reinterpret_cast<uint32_t*>(dst + off) = w[0];
-          *reinterpret_cast<uint32_t*>(dst + off + kPage * 16) = w[1];
-        }
-      }
     }
+    uint32_t keep = 0xFFFFFFFFu;   // code bytes of valid slots (the same for each word)
+    if (valid < kPage) {
+      // Slots past the valid count may hold anything: zeroed here they do not
+      // raise the maximum, and their codes are masked below.
+      uint32_t lo = 0, hi = 0;   // value masks of words 2 f and 2 f + 1
+      if (is_v) {
+        keep = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) keep |= 4 * grp + e < valid ? 0xFFu << (8 * e) : 0u;
+        lo = (keep & 0x000000FFu ? 0x0000FFFFu : 0u) | (keep & 0x0000FF00u ? 0xFFFF0000u : 0u);
+        hi = (keep & 0x00FF0000u ? 0x0000FFFFu : 0u) | (keep & 0xFF000000u ? 0xFFFF0000u : 0u);
+      } else {
+        keep = lo = hi = col < valid ? 0xFFFFFFFFu : 0u;
+      }
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[p][i] &= i & 1 ? hi : lo;
+    }
+    float amax = 0.f;
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(bf16_word(x[p], e)));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+    const float inv = amax > 0.f ? __fdiv_rn(448.f, amax) : 1.f;
+    uint8_t* dst = (is_v ? a.v_dst : a.k_dst) + tile + 16 * lane;
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+      u32x4 codes;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        int packed = __builtin_amdgcn_cvt_pk_fp8_f32(bf16_word(x[p], 4 * q) * inv, bf16_word(x[p], 4 * q + 1) * inv, 0,
+                                                     false);
+        packed = __builtin_amdgcn_cvt_pk_fp8_f32(bf16_word(x[p], 4 * q + 2) * inv, bf16_word(x[p], 4 * q + 3) * inv,
+                                                 packed, true);
+        codes[q] = uint32_t(packed) & keep;
+      }
+      __builtin_nontemporal_store(codes, reinterpret_cast<u32x4*>(dst + 1024 * p));
+    }
+    if (lane == 0)
+      (is_v ? a.v_scale : a.k_scale)[size_t(page) * a.num_kv_heads + kvh] = amax > 0.f ? __fdiv_rn(amax, 448.f) : 1.f;
   }
 }
 
@@ -1299,10 +1338,13 @@ hipError_t launch_combine(const CombineArgs& a, hipStream_t stream) {
 
 hipError_t launch_quantize_fp8(const QuantArgs& a, hipStream_t stream) {
   if (a.num_pages == 0) return hipSuccess;
+  const int64_t tiles = int64_t(a.num_pages) * a.num_kv_heads * 2;
+  const int64_t blocks = (tiles + kQuantWaves - 1) / kQuantWaves;
+  const dim3 grid(uint32_t(blocks < kQuantMaxBlocks ? blocks : kQuantMaxBlocks)), block(64 * kQuantWaves);
   if (a.head_dim == 128)
-    hipLaunchKernelGGL(quantize_fp8_kernel<128>, dim3(a.num_pages), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(quantize_fp8_kernel<128>, grid, block, 0, stream, a);
   else
-    hipLaunchKernelGGL(quantize_fp8_kernel<64>, dim3(a.num_pages), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(quantize_fp8_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

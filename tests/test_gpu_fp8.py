@@ -185,6 +185,23 @@ def test_quantizer_zero_tile_and_extremes():
     assert np.array_equal(k8, rk) and np.array_equal(v8, rv)
 
 
+@pytest.mark.parametrize("hkv,d", [(1, 64), (3, 64), (1, 128), (5, 128)])
+def test_quantizer_every_valid_count(hkv, d):
+    """Pages with 1 to 16 valid slots (the rest NaN), tile counts that do not
+    fill the last workgroup, tiny and large values: bit for bit."""
+    _say(f"fp8 quantizer hkv={hkv} d={d}")
+    batch = build_batch([16 * 19 + 5, *range(1, 17)], hkv, hkv, d, 31 + hkv, k_mult=1e-20)
+    pages, valid = page_fill(batch)
+    assert set(valid) == set(range(1, 17)) and pages.size % 2 == 0
+    pages, valid = pages[1:], valid[1:]
+    got = _quantize_gpu(batch, pages, valid)
+    want = [np.full(got[0].shape, 0xAA, np.uint8), np.full(got[1].shape, 0xAA, np.uint8),
+            np.full(got[2].shape, -1.0, np.float32), np.full(got[3].shape, -1.0, np.float32)]
+    fp8_ref.quantize_pages(bf16_bits(batch.k_pool), bf16_bits(batch.v_pool), pages, valid, *want)
+    for name, x, y in zip(("key codes", "value codes", "key scales", "value scales"), got, want):
+        assert np.array_equal(x, y), f"{name} differ"
+
+
 def test_quantize_then_attend_end_to_end():
     """The library's quantizer, then its fp8 attention, on the full 32B-like
     cache: every page's codes and scales against the oracle's quantizer bit
