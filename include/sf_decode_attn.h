@@ -407,6 +407,42 @@ sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info, c
                          float* lse, void* stream);
 
 /*
+ * Extend attention through a runner (sf_runner_create): plans, stores the new
+ * tokens if given, and attends, in one call. out, lse and the pools as
+ * sf_extend_attn; the runner's own plan differs from sf_extend_attn_plan's
+ * where that one would leave compute units idle: items of 128 rows instead of
+ * 384, and key walks cut into parts whose partial results a further launch
+ * merges. *info is what sf_extend_attn_plan reports for the same lengths.
+ *
+ * The call allocates nothing: *memory lends it pinned host memory (16-byte
+ * aligned, `slots` <= 32 equal slots of whole 32-byte rows, one plan each) and
+ * device memory, both the caller's and unchanged until the runner is
+ * destroyed or a call passes other memory (which first waits for the steps so
+ * far). If a slot or the device memory is too small the call launches
+ * nothing, writes the bytes it needs to need_slot and need_device and returns
+ * SF_ERR_CAPACITY. Calls on one runner must not overlap on the host; a call on
+ * another stream than the runner's last step waits for the steps so far.
+ * Asynchronous on stream. Other errors as sf_extend_attn_plan and
+ * sf_extend_attn; SF_ERR_UNSUPPORTED, with nothing launched, also on a stream
+ * that is being captured into a graph.
+ */
+typedef struct sf_runner_memory {
+  void* pinned;
+  uint64_t pinned_bytes;
+  void* device;
+  uint64_t device_bytes;
+  uint64_t need_slot;        /* out, with SF_ERR_CAPACITY */
+  uint64_t need_device;
+  int32_t slots;
+  int32_t reserved;
+} sf_runner_memory;
+
+sf_status sf_runner_extend(sf_runner* runner, const sf_attn_desc* desc, const int32_t* seq_lens_host,
+                           const int32_t* q_lens_host, const void* q, const void* k_new, const void* v_new,
+                           void* k_pool, void* v_pool, const int32_t* block_table, float* out, float* lse,
+                           sf_runner_memory* memory, void* stream, sf_extend_info* info);
+
+/*
  * Host page allocator for the KV pool. A trajectory's cache grows by one
  * 16-token page at a time and is released when it leaves, within a pool of
  * fixed size (the KV-cache budget of Sec. 5.2). Pages are ids 0 .. N-1 of
@@ -532,6 +568,20 @@ double sf_cost_ideal_gain(const sf_cost_model* model, double length);
 sf_status sf_route(const sf_cost_model* model, double mu, int32_t min_initial_version,
                    sf_instance_state* inst, int32_t num_inst, const sf_trajectory* trajs,
                    int32_t num_trajs, int32_t* target, int32_t* num_routed);
+
+/*
+ * Test support: the plan sf_runner_extend makes for a device of num_cus
+ * compute units (0: the default), host only. counts[0..4] = rows per item,
+ * parts, merges, stores, partial slots; rows of 8 ints in that order:
+ * parts  seq, kv_head, first step, tokens, position of the item's first token,
+ *        its query row, end step, partial slot + 1 (0: written to out)
+ * merges first slot, parts, tokens, first query row, kv_head
+ * stores seq, first page, pages, first new position, end position, query row
+ *        of the first new position (none if store is 0)
+ */
+sf_status sf_debug_extend_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host,
+                               const int32_t* q_lens_host, int32_t num_cus, int32_t store, int32_t* work_host,
+                               uint64_t work_capacity_bytes, int32_t* counts);
 
 /*
  * Test support: copies the cached keys and values of tokens 0 .. len-1 of

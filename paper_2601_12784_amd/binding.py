@@ -24,6 +24,7 @@ ITEM_INTS = 8
 
 STATUS = {0: "SF_OK", 1: "SF_ERR_INVALID_ARG", 2: "SF_ERR_UNSUPPORTED", 3: "SF_ERR_CAPACITY",
           4: "SF_ERR_PLAN_MISMATCH", 5: "SF_ERR_HIP"}
+UNSUPPORTED, CAPACITY = 2, 3
 
 
 class SfError(RuntimeError):
@@ -63,6 +64,12 @@ class sf_runner_extras(ctypes.Structure):
     _fields_ = [("k_new", ctypes.c_void_p), ("v_new", ctypes.c_void_p), ("new_pages_host", ctypes.c_void_p),
                 ("k_scale", ctypes.c_void_p), ("v_scale", ctypes.c_void_p), ("attn_start", ctypes.c_void_p),
                 ("attn_end", ctypes.c_void_p)]
+
+
+class sf_runner_memory(ctypes.Structure):
+    _fields_ = [("pinned", ctypes.c_void_p), ("pinned_bytes", ctypes.c_uint64), ("device", ctypes.c_void_p),
+                ("device_bytes", ctypes.c_uint64), ("need_slot", ctypes.c_uint64), ("need_device", ctypes.c_uint64),
+                ("slots", ctypes.c_int32), ("reserved", ctypes.c_int32)]
 
 
 class sf_cost_model(ctypes.Structure):
@@ -116,6 +123,9 @@ def lib():
     L.sf_kv_quantize_fp8.argtypes = [P(sf_attn_desc), vp, vp, vp, vp, ctypes.c_int32, vp, vp, vp, vp, vp]
     L.sf_extend_attn_plan.argtypes = [P(sf_attn_desc), vp, vp, vp, ctypes.c_uint64, P(sf_extend_info)]
     L.sf_extend_attn.argtypes = [P(sf_attn_desc), P(sf_extend_info), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    L.sf_runner_extend.argtypes = [vp, P(sf_attn_desc), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, P(sf_runner_memory),
+                                   vp, P(sf_extend_info)]
+    L.sf_debug_extend_plan.argtypes = [P(sf_attn_desc), vp, vp, ctypes.c_int32, ctypes.c_int32, vp, ctypes.c_uint64, vp]
     L.sf_page_pool_create.argtypes = [ctypes.c_int32, P(vp)]
     L.sf_page_pool_destroy.argtypes = [vp]
     L.sf_page_pool_destroy.restype = None
@@ -138,7 +148,7 @@ def lib():
                "sf_decode_attn_append", "sf_page_pool_create", "sf_page_pool_claim", "sf_page_pool_alloc",
                "sf_page_pool_release", "sf_page_table_step", "sf_route", "sf_extend_attn_plan",
                "sf_extend_attn", "sf_decode_attn_fp8", "sf_kv_quantize_fp8", "sf_runner_create",
-               "sf_runner_step", "sf_debug_stream_read", "sf_decode_attn_scratch"):
+               "sf_runner_step", "sf_runner_extend", "sf_debug_extend_plan", "sf_debug_stream_read", "sf_decode_attn_scratch"):
         getattr(L, fn).restype = ctypes.c_int
     L.sf_status_string.argtypes = [ctypes.c_int]
     L.sf_status_string.restype = ctypes.c_char_p
@@ -379,26 +389,31 @@ def sf_extend_attn_plan(desc: sf_attn_desc, seq_lens, q_lens, work_host=None):
     return info, work_host
 
 
+def _check_extend(desc, rows, q, k_pool, v_pool, block_table, out, lse, k_new, v_new):
+    """The tensors of an extend call over `rows` new tokens."""
+    hq, hkv, d = desc.num_q_heads, desc.num_kv_heads, desc.head_dim
+    _dev(q, "q", torch.bfloat16, (rows, hq, d))
+    _dev(k_pool, "k_pool", torch.bfloat16, (desc.num_pages, hkv, d // 8, PAGE, 8))
+    _dev(v_pool, "v_pool", torch.bfloat16, (desc.num_pages, hkv, d, PAGE))
+    _dev(block_table, "block_table", torch.int32, (desc.num_seqs, desc.block_table_stride))
+    _dev(out, "out", torch.float32, (rows, hq, d))
+    if lse is not None:
+        _dev(lse, "lse", torch.float32, (rows, hq))
+    if (k_new is None) != (v_new is None):
+        raise ValueError("give both k_new and v_new, or neither")
+    if k_new is not None:
+        _dev(k_new, "k_new", torch.bfloat16, (rows, hkv, d))
+        _dev(v_new, "v_new", torch.bfloat16, (rows, hkv, d))
+
+
 def sf_extend_attn(desc, info, work_host, work_dev, q, k_pool, v_pool, block_table, out, lse=None,
                    k_new=None, v_new=None, stream=None):
     """Enqueues extend attention (after the store of k_new / v_new into the
     pools when both are given). q, out: [T, Hq, D]; k_new, v_new: [T, Hkv, D]."""
-    t, hq, hkv, d = info.num_q_rows, desc.num_q_heads, desc.num_kv_heads, desc.head_dim
-    _dev(q, "q", torch.bfloat16, (t, hq, d))
-    _dev(k_pool, "k_pool", torch.bfloat16, (desc.num_pages, hkv, d // 8, PAGE, 8))
-    _dev(v_pool, "v_pool", torch.bfloat16, (desc.num_pages, hkv, d, PAGE))
-    _dev(block_table, "block_table", torch.int32, (desc.num_seqs, desc.block_table_stride))
-    _dev(out, "out", torch.float32, (t, hq, d))
+    _check_extend(desc, info.num_q_rows, q, k_pool, v_pool, block_table, out, lse, k_new, v_new)
     _dev(work_dev, "work_dev", torch.int32)
     if work_dev.numel() * 4 < info.work_bytes:
         raise ValueError("work_dev is smaller than the plan")
-    if lse is not None:
-        _dev(lse, "lse", torch.float32, (t, hq))
-    if (k_new is None) != (v_new is None):
-        raise ValueError("give both k_new and v_new, or neither")
-    if k_new is not None:
-        _dev(k_new, "k_new", torch.bfloat16, (t, hkv, d))
-        _dev(v_new, "v_new", torch.bfloat16, (t, hkv, d))
     _check("sf_extend_attn", lib().sf_extend_attn(
         ctypes.byref(desc), ctypes.byref(info), _addr(work_host), _addr(work_dev), _addr(q), _addr(k_new),
         _addr(v_new), _addr(k_pool), _addr(v_pool), _addr(block_table), _addr(out), _addr(lse),
@@ -408,25 +423,83 @@ def sf_extend_attn(desc, info, work_host, work_dev, q, k_pool, v_pool, block_tab
 class ExtendAttention:
     """Plans and launches extend attention for one batch of re-prefills.
 
-    The work list is planned on the host at each call, written into a pinned
-    buffer and uploaded with the launch; everything else runs in the
-    library's kernels. Before the pinned buffer is rewritten, the call waits
-    for the event recorded after the previous upload, so a queued copy never
-    reads a half-written list."""
+    Each call goes through a native runner (sf_runner_extend): it plans into
+    pinned memory that the launches read in place, so calls queue up behind
+    each other without waiting. The pinned slots and the device memory for
+    partial results are torch tensors that this object keeps and lends to the
+    runner. A stream that is being captured into a graph takes sf_extend_attn
+    instead, on a work list that is uploaded with the launch; before that list
+    is rewritten, the call waits for the event recorded after the previous
+    upload."""
 
     def __init__(self, num_q_heads, num_kv_heads, head_dim, device=None):
         self.hq, self.hkv, self.d = int(num_q_heads), int(num_kv_heads), int(head_dim)
         self.device = torch.device("cuda") if device is None else torch.device(device)
+        self._L = None
+        self._runner = ctypes.c_void_p()
+        self._memory = sf_runner_memory()
+        self._lent = None
         self._work_host = None
         self._work_dev = None
         self._uploaded = None
         self.last_info = None
 
+    def _create(self):
+        self._L = lib()
+        shape = make_desc(0, self.hq, self.hkv, self.d, 1, 0, 1.0)
+        with torch.cuda.device(self.device):
+            opts = make_opts(num_cus=torch.cuda.get_device_properties(self.device).multi_processor_count)
+            _check("sf_runner_create", self._L.sf_runner_create(ctypes.byref(shape), ctypes.byref(opts),
+                                                                ctypes.byref(self._runner)))
+
+    def _lend(self, stream):
+        """Larger memory for the runner, as its last call asked. What it held
+        stays alive until the next call has waited for the steps that use it."""
+        m = self._memory
+        need = int(m.need_slot)
+        slots = 32 if need <= 1 << 14 else 8 if need <= 1 << 18 else 4
+        slot = max(int(m.pinned_bytes) // m.slots if m.slots else 0, (need + need // 4 + 1023) // 32 * 32)
+        device = max(int(m.device_bytes), int(m.need_device) * 5 // 4 + 4096)
+        pinned = torch.empty(slots * slot, dtype=torch.uint8, pin_memory=True)
+        work = torch.empty(device, dtype=torch.uint8, device=self.device)
+        if stream is not None:   # the allocation is ordered on the current stream
+            torch.cuda.current_stream(self.device).synchronize()
+        m.pinned, m.pinned_bytes, m.slots = pinned.data_ptr(), slots * slot, slots
+        m.device, m.device_bytes = work.data_ptr(), device
+        return pinned, work
+
     def __call__(self, q, k_pool, v_pool, block_table, seq_lens, q_lens, scale, out=None, lse=None,
                  k_new=None, v_new=None, stream=None):
         lens = np.ascontiguousarray(np.asarray(seq_lens), dtype=np.int32)
         qls = np.ascontiguousarray(np.asarray(q_lens), dtype=np.int32)
+        if lens.ndim != 1 or lens.shape != qls.shape:
+            raise ValueError("seq_lens and q_lens must have num_seqs entries")
         desc = make_desc(lens.size, self.hq, self.hkv, self.d, block_table.shape[1], k_pool.shape[0], scale)
+        if self._L is None:
+            self._create()
+        rows = int(qls.sum())
+        if DEBUG_CHECKS:
+            check_block_table(desc, block_table, np.where(qls > 0, lens, 0))
+        if out is None:
+            out = torch.empty((rows, self.hq, self.d), dtype=torch.float32, device=self.device)
+        _check_extend(desc, rows, q, k_pool, v_pool, block_table, out, lse, k_new, v_new)
+        info = sf_extend_info()
+        args = (self._runner, ctypes.byref(desc), lens.ctypes.data, qls.ctypes.data, _addr(q), _addr(k_new),
+                _addr(v_new), _addr(k_pool), _addr(v_pool), _addr(block_table), _addr(out), _addr(lse),
+                ctypes.byref(self._memory), _stream(stream), ctypes.byref(info))
+        st = self._L.sf_runner_extend(*args)
+        if st == CAPACITY:
+            lent = self._lend(stream)
+            st = self._L.sf_runner_extend(*args)
+            self._lent = lent
+        if st == UNSUPPORTED:
+            info = self._call_captured(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream)
+        else:
+            _check("sf_runner_extend", st)
+        self.last_info = info
+        return out
+
+    def _call_captured(self, desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream):
         info = sf_extend_info()
         _check("sf_extend_attn_plan", lib().sf_extend_attn_plan(ctypes.byref(desc), lens.ctypes.data,
                                                                 qls.ctypes.data, None, 0, ctypes.byref(info)))
@@ -437,17 +510,18 @@ class ExtendAttention:
             self._work_host = torch.empty(need, dtype=torch.int32, pin_memory=True)
             self._work_dev = torch.empty(need, dtype=torch.int32, device=self.device)
         info, _ = sf_extend_attn_plan(desc, lens, qls, work_host=self._work_host)
-        if DEBUG_CHECKS:
-            check_block_table(desc, block_table, np.where(qls > 0, lens, 0))
-        if out is None:
-            out = torch.empty((info.num_q_rows, self.hq, self.d), dtype=torch.float32, device=self.device)
         sf_extend_attn(desc, info, self._work_host, self._work_dev, q, k_pool, v_pool, block_table, out, lse,
                        k_new=k_new, v_new=v_new, stream=stream)
         ev = torch.cuda.Event()
         ev.record(stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.current_stream())
         self._uploaded = ev
-        self.last_info = info
-        return out
+        return info
+
+    def __del__(self):
+        r = getattr(self, "_runner", None)
+        if r is not None and r.value:
+            self._L.sf_runner_destroy(r)   # waits for the steps that use the lent memory
+            r.value = None
 
 
 class PagePool:

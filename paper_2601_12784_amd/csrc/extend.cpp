@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <vector>
 
 #include "sf_internal.h"
@@ -27,24 +28,43 @@ struct Item {
   int32_t seq, kvh, t0, nt, prefix, qrow0, steps;
 };
 
+// Checks the lengths and counts the query rows.
+sf_status check_lengths(const sf_attn_desc* desc, const int32_t* seq_lens_host, const int32_t* q_lens_host,
+                        int64_t* rows) {
+  sf_status st = validate_desc(desc);
+  if (st != SF_OK) return st;
+  if (desc->num_seqs > 0 && (!seq_lens_host || !q_lens_host)) return SF_ERR_INVALID_ARG;
+  *rows = 0;
+  for (int32_t s = 0; s < desc->num_seqs; ++s) {
+    const int32_t L = seq_lens_host[s], e = q_lens_host[s];
+    if (e < 0 || L < e || int64_t(L) > int64_t(kPage) * desc->block_table_stride) return SF_ERR_INVALID_ARG;
+    if (L > 0 && desc->num_pages == 0) return SF_ERR_INVALID_ARG;
+    *rows += e;
+  }
+  if (*rows > INT32_MAX / (int64_t(desc->num_q_heads) * desc->head_dim)) return SF_ERR_INVALID_ARG;
+  return SF_OK;
+}
+
+void fill_info(const sf_attn_desc* desc, int64_t items, int64_t rows, sf_extend_info* info) {
+  info->num_items = int32_t(items);
+  info->tokens_per_item = kExtendRows / (desc->num_q_heads / desc->num_kv_heads);
+  info->num_q_rows = int32_t(rows);
+  info->reserved = 0;
+  info->work_bytes = uint64_t(items) * kItemInts * 4;
+  info->desc_key = desc_key(desc);
+}
+
 }  // namespace
 
 extern "C" sf_status sf_extend_attn_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host,
                                          const int32_t* q_lens_host, int32_t* work_host,
                                          uint64_t work_capacity_bytes, sf_extend_info* info) {
+  int64_t rows = 0;
   sf_status st = validate_desc(desc);
   if (st != SF_OK) return st;
-  if (!info || (desc->num_seqs > 0 && (!seq_lens_host || !q_lens_host))) return SF_ERR_INVALID_ARG;
-  const int32_t g = desc->num_q_heads / desc->num_kv_heads;
-  const int32_t per_item = kExtendRows / g;
-  int64_t rows = 0;
-  for (int32_t s = 0; s < desc->num_seqs; ++s) {
-    const int32_t L = seq_lens_host[s], e = q_lens_host[s];
-    if (e < 0 || L < e || int64_t(L) > int64_t(kPage) * desc->block_table_stride) return SF_ERR_INVALID_ARG;
-    if (L > 0 && desc->num_pages == 0) return SF_ERR_INVALID_ARG;
-    rows += e;
-  }
-  if (rows > INT32_MAX / (int64_t(desc->num_q_heads) * desc->head_dim)) return SF_ERR_INVALID_ARG;
+  if (!info) return SF_ERR_INVALID_ARG;
+  if ((st = check_lengths(desc, seq_lens_host, q_lens_host, &rows)) != SF_OK) return st;
+  const int32_t per_item = kExtendRows / (desc->num_q_heads / desc->num_kv_heads);
 
   std::vector<Item> items;
   int32_t qrow0 = 0;
@@ -61,12 +81,7 @@ extern "C" sf_status sf_extend_attn_plan(const sf_attn_desc* desc, const int32_t
   // Longest key walk first; ties keep (sequence, KV head, block) order.
   std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.steps > y.steps; });
 
-  info->num_items = int32_t(items.size());
-  info->tokens_per_item = per_item;
-  info->num_q_rows = int32_t(rows);
-  info->reserved = 0;
-  info->work_bytes = uint64_t(items.size()) * kItemInts * 4;
-  info->desc_key = desc_key(desc);
+  fill_info(desc, int64_t(items.size()), rows, info);
   if (!work_host) return SF_OK;
   if (work_capacity_bytes < info->work_bytes) return SF_ERR_CAPACITY;
   for (size_t i = 0; i < items.size(); ++i) {
@@ -84,33 +99,221 @@ extern "C" sf_status sf_extend_attn_plan(const sf_attn_desc* desc, const int32_t
   return SF_OK;
 }
 
-extern "C" sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info,
-                                    const int32_t* work_host, int32_t* work_dev, const void* q,
-                                    const void* k_new, const void* v_new, void* k_pool, void* v_pool,
-                                    const int32_t* block_table, float* out, float* lse, void* stream) {
-  sf_status st = validate_desc(desc);
+namespace {
+
+constexpr int32_t kStepKeys = 2 * kPage;
+
+// Calls f(sequence, first new token, tokens, steps) for every block of at
+// most `per` new tokens (each is one item per KV head).
+template <class F>
+void for_blocks(const sf_attn_desc* desc, const int32_t* lens, const int32_t* new_lens, int32_t per, F f) {
+  for (int32_t s = 0; s < desc->num_seqs; ++s)
+    for (int32_t t0 = 0; t0 < new_lens[s]; t0 += per) {
+      const int32_t nt = std::min(per, new_lens[s] - t0);
+      f(s, t0, nt, (lens[s] - new_lens[s] + t0 + nt + kStepKeys - 1) / kStepKeys);
+    }
+}
+
+// How sf_runner_extend cuts its work: rows per item, and the longest part of a
+// key walk (steps).
+struct Split {
+  int32_t rows;
+  int32_t most;
+};
+
+// The cut is chosen by estimated time. A workgroup takes kStart + kStep *
+// steps (us at D = 128; half the step at D = 64), measured with one 384-row
+// item per CU (12 waves) and one or two 128-row items per CU (4 waves each):
+// one 16384-token walk cut into 1, 2, 4 .. 32 parts took 582, 295, 154, 84, 50,
+// 35 us with 384 rows and 486, 250, 128, 69, 39, 32 us with 128. kStart holds
+// the launch, the first loads and the result's store. Cut walks add the merge
+// launch: kMerge plus the partial rows' bytes. Uncut 384-row items are best
+// whenever they fill the chip several times over; short grids gain from parts
+// that fill it once (or 2 .. 4 times): 4 sequences with 256 new tokens after
+// 8000 cached ones, 28/4 heads, 305 us whole, 130 + 11 us in parts of 88 steps,
+// 156 + 21 in parts of 32; one prompt of 1000 tokens 48 us whole, 38 us as
+// whole 128-row items, 26 + 5 us as 128-row items in parts of at most 16 steps.
+struct Cost {
+  double start, step;
+};
+constexpr Cost kLarge = {14.0, 1.12}, kSmallAlone = {10.0, 0.94}, kSmallPaired = {16.0, 1.0};
+constexpr double kMerge = 4.0, kMergeBytesPerUs = 4.4e6;
+constexpr int32_t kSmallestPart = 4;   // steps
+constexpr int32_t kRounds = 4;
+
+struct Totals {
+  int64_t parts = 0, steps = 0, cut_rows = 0;
+  int32_t longest = 0, shortest = INT32_MAX;
+};
+
+Split choose_split(const sf_attn_desc* desc, const int32_t* lens, const int32_t* new_lens, int32_t num_cus) {
+  const int32_t g = desc->num_q_heads / desc->num_kv_heads;
+  const int64_t hkv = desc->num_kv_heads;
+  const double step_scale = desc->head_dim / 128.0;
+  auto totals = [&](int32_t rows, int32_t most) {
+    Totals t;
+    const float inv = 1.f / float(most);   // an estimate: the plan itself counts exactly
+    for_blocks(desc, lens, new_lens, rows / g, [&](int32_t, int32_t, int32_t nt, int32_t steps) {
+      const int32_t k = steps <= most ? 1 : int32_t(float(steps - 1) * inv) + 1;
+      const int32_t len = k == 1 ? steps : int32_t(float(steps) / float(k));
+      t.parts += k;
+      t.steps += steps;
+      if (k > 1) t.cut_rows += int64_t(k) * nt * g;
+      t.longest = std::max(t.longest, k == 1 ? steps : len + 1);
+      t.shortest = std::min(t.shortest, len);
+    });
+    t.parts *= hkv;
+    t.steps *= hkv;
+    t.cut_rows *= hkv;
+    return t;
+  };
+  // Estimated time of a plan on `slots` concurrent workgroups: no less than
+  // its longest part, and its average load plus what a partial last round of
+  // the shortest parts leaves idle.
+  auto estimate = [&](const Totals& t, bool small) {
+    // 128-row items: one per CU, two per CU, or in between
+    const double pair = std::min(1.0, std::max(0.0, double(t.parts) / num_cus - 1.0));
+    const Cost c = small ? Cost{kSmallAlone.start + pair * (kSmallPaired.start - kSmallAlone.start),
+                                kSmallAlone.step + pair * (kSmallPaired.step - kSmallAlone.step)}
+                         : kLarge;
+    const int64_t slots = small ? 2 * num_cus : num_cus;
+    const double step = c.step * step_scale;
+    const int64_t rest = t.parts % slots;
+    const double idle = rest ? 1.0 - double(rest) / double(slots) : 0.0;
+    const double load = (double(t.parts) * c.start + step * double(t.steps)) / double(slots);
+    return std::max(c.start + step * t.longest, load + idle * (c.start + step * t.shortest)) +
+           (t.cut_rows ? kMerge + double(t.cut_rows) * desc->head_dim * 4 / kMergeBytesPerUs : 0.0);
+  };
+
+  Split best = {kExtendRows, INT32_MAX};
+  const Totals whole = totals(kExtendRows, INT32_MAX);
+  if (whole.parts == 0 || whole.parts > int64_t(kRounds) * 2 * num_cus) return best;
+  double best_us = estimate(whole, false);
+  auto consider = [&](int32_t rows, const Totals& uncut) {
+    const bool small = rows == kExtendSmallRows;
+    auto take = [&](const Totals& t, int32_t most) {
+      const double us = estimate(t, small);
+      if (us < best_us) best_us = us, best = {rows, most};
+    };
+    take(uncut, INT32_MAX);
+    const int64_t slots = small ? 2 * num_cus : num_cus;
+    for (int32_t r = 1; r <= kRounds; ++r) {
+      // the shortest parts that number at most r per slot, and somewhat longer ones
+      if (uncut.parts >= r * slots) continue;
+      double most = std::max<double>(kSmallestPart, double(uncut.steps) / double(r * slots));
+      Totals t;
+      for (; most < uncut.longest; most = std::max(most + 1.0, most * 1.03))
+        if ((t = totals(rows, int32_t(most))).parts <= r * slots) break;
+      if (most >= uncut.longest) continue;
+      take(t, int32_t(most));
+      for (const double longer : {1.25, 1.6})
+        if (longer * most < uncut.longest) take(totals(rows, int32_t(longer * most)), int32_t(longer * most));
+    }
+  };
+  consider(kExtendRows, whole);
+  if (whole.parts <= 2 * num_cus) consider(kExtendSmallRows, totals(kExtendSmallRows, INT32_MAX));
+  return best;
+}
+
+}  // namespace
+
+sf_status sf::extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_lens_host, const int32_t* q_lens_host,
+                                int32_t num_cus, bool store, int32_t* work, uint64_t capacity, ExtendPlan* plan,
+                                sf_extend_info* info) {
+  int64_t q_rows = 0;
+  sf_status st = check_lengths(desc, seq_lens_host, q_lens_host, &q_rows);
   if (st != SF_OK) return st;
-  if (!info) return SF_ERR_INVALID_ARG;
-  if (info->desc_key != desc_key(desc)) return SF_ERR_PLAN_MISMATCH;
-  if (info->num_items < 0 || info->num_q_rows < 0 || info->reserved != 0 ||
-      info->work_bytes != uint64_t(info->num_items) * kItemInts * 4 ||
-      info->tokens_per_item != kExtendRows / (desc->num_q_heads / desc->num_kv_heads))
-    return SF_ERR_PLAN_MISMATCH;
-  if (info->num_items == 0) return SF_OK;
+  const int32_t g = desc->num_q_heads / desc->num_kv_heads, hkv = desc->num_kv_heads;
+  const int32_t *lens = seq_lens_host, *news = q_lens_host;
+
+  int64_t items = 0;
+  for (int32_t s = 0; s < desc->num_seqs; ++s) items += (news[s] + kExtendRows / g - 1) / (kExtendRows / g);
+  fill_info(desc, items * hkv, q_rows, info);
+
+  const Split split = choose_split(desc, lens, news, num_cus > 0 ? num_cus : kDefaultNumCus);
+  const int32_t rows = split.rows, most = split.most;
+  const int32_t per = rows / g;
+  auto parts_of = [&](int32_t steps) { return (int64_t(steps) + most - 1) / most; };
+  int64_t parts = 0, merges = 0, slots = 0, longest = 0;
+  for_blocks(desc, lens, news, per, [&](int32_t, int32_t, int32_t, int32_t steps) {
+    const int64_t k = parts_of(steps);
+    parts += k * hkv;
+    if (k > 1) {
+      merges += hkv;
+      slots += k * hkv;
+    }
+    longest = std::max<int64_t>(longest, (steps + k - 1) / k);
+  });
+  int64_t stores = 0, store_pages = 0;
+  if (store)
+    for (int32_t s = 0; s < desc->num_seqs; ++s)
+      if (news[s] > 0) store_pages += (lens[s] + kPage - 1) / kPage - (lens[s] - news[s]) / kPage;
+  const int32_t run = store_pages > 2048 ? 4 : 1;
+  if (store)
+    for (int32_t s = 0; s < desc->num_seqs; ++s)
+      if (news[s] > 0) stores += ((lens[s] + kPage - 1) / kPage - (lens[s] - news[s]) / kPage + run - 1) / run;
+  if (parts + merges + stores > INT32_MAX / kItemInts) return SF_ERR_INVALID_ARG;
+  plan->rows = rows;
+  plan->num_parts = int32_t(parts);
+  plan->num_merge = int32_t(merges);
+  plan->num_store = int32_t(stores);
+  plan->num_slots = int32_t(slots);
+  if (capacity < plan->bytes()) return SF_ERR_CAPACITY;
+
+  // Part rows, longest first (a counting sort by length; ties keep the order
+  // block, KV head, part).
+  thread_local std::vector<int32_t> at;
+  at.assign(size_t(longest) + 2, 0);
+  auto each_part = [&](auto f) {
+    int32_t s_prev = 0;
+    int64_t qrow0 = 0;
+    for_blocks(desc, lens, news, per, [&](int32_t s, int32_t t0, int32_t nt, int32_t steps) {
+      for (; s_prev < s; ++s_prev) qrow0 += news[s_prev];
+      const int64_t k = parts_of(steps);
+      for (int32_t h = 0; h < hkv; ++h) f(s, h, lens[s] - news[s] + t0, nt, int32_t(qrow0 + t0), steps, k);
+    });
+  };
+  each_part([&](int32_t, int32_t, int32_t, int32_t, int32_t, int32_t steps, int64_t k) {
+    for (int64_t i = 0; i < k; ++i) ++at[size_t(longest - ((i + 1) * steps / k - i * steps / k)) + 1];
+  });
+  for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+  int32_t slot = 0, merge = 0;
+  int32_t* merge_rows = work + parts * kItemInts;
+  each_part([&](int32_t s, int32_t h, int32_t first, int32_t nt, int32_t qrow, int32_t steps, int64_t k) {
+    if (k > 1) {
+      const int32_t m8[kItemInts] = {slot, int32_t(k), nt, qrow, h, 0, 0, 0};
+      std::memcpy(merge_rows + int64_t(merge++) * kItemInts, m8, sizeof m8);
+    }
+    for (int64_t i = 0; i < k; ++i) {
+      const int32_t b = int32_t(i * steps / k), e = int32_t((i + 1) * steps / k);
+      const int32_t r8[kItemInts] = {s, h, b, nt, first, qrow, e, k > 1 ? ++slot : 0};
+      std::memcpy(work + int64_t(at[size_t(longest - (e - b))]++) * kItemInts, r8, sizeof r8);
+    }
+  });
+  if (store) {
+    int32_t* r = merge_rows + merges * kItemInts;
+    int32_t qrow0 = 0;
+    for (int32_t s = 0; s < desc->num_seqs; qrow0 += news[s++]) {
+      const int32_t first = lens[s] - news[s], end_page = (lens[s] + kPage - 1) / kPage;
+      for (int32_t p = first / kPage; news[s] > 0 && p < end_page; p += run, r += kItemInts) {
+        const int32_t r8[kItemInts] = {s, p, std::min(run, end_page - p), first, lens[s], qrow0, 0, 0};
+        std::memcpy(r, r8, sizeof r8);
+      }
+    }
+  }
+  return SF_OK;
+}
+
+sf_status sf::extend_args(const sf_attn_desc* desc, const int32_t* work_dev, const void* q, const void* k_new,
+                          const void* v_new, void* k_pool, void* v_pool, const int32_t* block_table, float* out,
+                          float* lse, ExtendArgs* args) {
   if ((k_new == nullptr) != (v_new == nullptr)) return SF_ERR_INVALID_ARG;
   if (!work_dev || !q || !k_pool || !v_pool || !block_table || !out) return SF_ERR_INVALID_ARG;
   if (!aligned16(work_dev) || !aligned16(q) || !aligned16(k_pool) || !aligned16(v_pool) || !aligned16(out) ||
       !aligned4(block_table) || (lse && !aligned4(lse)) || (k_new && (!aligned16(k_new) || !aligned16(v_new))))
     return SF_ERR_INVALID_ARG;
-
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (work_host) {
-    hipError_t e = hipMemcpyAsync(work_dev, work_host, info->work_bytes, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return SF_ERR_HIP;
-  }
-  ExtendArgs a;
+  ExtendArgs a = {};
   a.items = work_dev;
-  a.num_items = info->num_items;
   a.q = static_cast<const uint16_t*>(q);
   a.k_pool = static_cast<const uint16_t*>(k_pool);
   a.v_pool = static_cast<const uint16_t*>(v_pool);
@@ -129,5 +332,44 @@ extern "C" sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_in
   a.v_new = static_cast<const uint16_t*>(v_new);
   a.k_dst = static_cast<uint16_t*>(k_pool);
   a.v_dst = static_cast<uint16_t*>(v_pool);
+  *args = a;
+  return SF_OK;
+}
+
+extern "C" sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info,
+                                    const int32_t* work_host, int32_t* work_dev, const void* q,
+                                    const void* k_new, const void* v_new, void* k_pool, void* v_pool,
+                                    const int32_t* block_table, float* out, float* lse, void* stream) {
+  sf_status st = validate_desc(desc);
+  if (st != SF_OK) return st;
+  if (!info) return SF_ERR_INVALID_ARG;
+  if (info->desc_key != desc_key(desc)) return SF_ERR_PLAN_MISMATCH;
+  if (info->num_items < 0 || info->num_q_rows < 0 || info->reserved != 0 ||
+      info->work_bytes != uint64_t(info->num_items) * kItemInts * 4 ||
+      info->tokens_per_item != kExtendRows / (desc->num_q_heads / desc->num_kv_heads))
+    return SF_ERR_PLAN_MISMATCH;
+  if (info->num_items == 0) return SF_OK;
+  ExtendArgs a;
+  if ((st = extend_args(desc, work_dev, q, k_new, v_new, k_pool, v_pool, block_table, out, lse, &a)) != SF_OK)
+    return st;
+  a.num_items = info->num_items;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (work_host) {
+    hipError_t e = hipMemcpyAsync(work_dev, work_host, info->work_bytes, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return SF_ERR_HIP;
+  }
   return launch_extend(a, s) == hipSuccess ? SF_OK : SF_ERR_HIP;
+}
+
+extern "C" sf_status sf_debug_extend_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host,
+                                          const int32_t* q_lens_host, int32_t num_cus, int32_t store,
+                                          int32_t* work_host, uint64_t work_capacity_bytes, int32_t* counts) {
+  if (!counts || num_cus < 0 || (work_capacity_bytes > 0 && !work_host)) return SF_ERR_INVALID_ARG;
+  ExtendPlan plan = {};
+  sf_extend_info info;
+  const sf_status st = extend_plan_parts(desc, seq_lens_host, q_lens_host, num_cus, store != 0, work_host,
+                                         work_capacity_bytes, &plan, &info);
+  const int32_t c[5] = {plan.rows, plan.num_parts, plan.num_merge, plan.num_store, plan.num_slots};
+  std::memcpy(counts, c, sizeof c);
+  return st;
 }

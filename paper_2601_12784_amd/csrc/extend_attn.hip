@@ -62,14 +62,34 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(4))) const int32_t* const_i32_ptr;
 
 constexpr float kLn2 = 0.69314718055994530942f;
-constexpr int kWaves = 12;
-constexpr int kStageWaves = 8;    // waves that stage K and V (the other four only compute)
-constexpr int kThreads = 64 * kWaves;
 constexpr int kRowTiles = 2;      // 16-row MFMA tiles per wave
 constexpr int kStepKeys = 2 * kPage;   // keys per step (two pages)
-constexpr int kSub = 1;                // steps per barrier interval
 constexpr float kRescaleMax = 32768.f; // headroom of the lazily moved softmax reference, 2^15 (fp16 weights)
-static_assert(kWaves * kRowTiles * 16 == kExtendRows, "rows per item");
+
+// The two builds of the attention kernel, by waves per workgroup (32 rows each).
+// Twelve waves (384 rows) are the throughput build: three waves per SIMD and
+// the least staging per row. Four waves (128 rows, two workgroups per CU) are
+// for grids too short for it: three times the items, and a lone step takes
+// 0.94 us against 1.12, since each wave has a SIMD to itself; fetching two
+// steps ahead is worth 20 % there (one 16384-token walk: 486 against 597 us)
+// and spills 10 registers in the other. Six waves (192 rows, two workgroups
+// per CU) leave the SIMDs with 2, 2, 1 and 1 waves per workgroup: 1.8 times
+// the time of twelve on a full re-prefill.
+template <int kWaves>
+struct Build;
+template <>
+struct Build<12> {
+  static constexpr int kStageWaves = 8;   // waves that stage K and V (the other four only compute)
+  static constexpr int kAhead = 1;        // steps fetched ahead of the one being computed
+  static constexpr int kPerSimd = 3;      // waves per SIMD
+};
+template <>
+struct Build<4> {
+  static constexpr int kStageWaves = 4;
+  static constexpr int kAhead = 2;
+  static constexpr int kPerSimd = 2;
+};
+static_assert(12 * kRowTiles * 16 == kExtendRows && 4 * kRowTiles * 16 == kExtendSmallRows, "rows per item");
 
 __device__ __forceinline__ const_i32_ptr as_constant(const int32_t* p) { return (const_i32_ptr)(p); }
 
@@ -107,7 +127,7 @@ __device__ __forceinline__ size_t tile_base(int32_t page, int32_t num_kv_heads, 
 // distinct 16-byte bank groups.
 __device__ __forceinline__ int v_swizzle(int d) { return (d >> 1) & 3; }
 
-template <int D>
+template <int D, int kStageWaves>
 struct Tiles {
   static constexpr int kElems = kPage * D;            // bf16 per (page, KV head) tile
   static constexpr int kChunks = kElems / 8;          // 16-byte pieces per tile
@@ -187,7 +207,8 @@ __device__ __forceinline__ u32x4 settle(TileWeights& t, float c, float& m, float
     const float mx_s = mx * c;
     const bool grow = mx_s > m;   // NaN (fully masked, zero scale) compares false
     const float mnew = grow ? mx_s : m;
-    const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+    // (a part of a walk may hold no key of a row at all: m stays -inf)
+    const float alpha = mnew == -__builtin_inff() ? 1.f : __builtin_amdgcn_exp2f(m - mnew);
     m = mnew;
     lsum *= alpha;
 #pragma unroll
@@ -206,24 +227,32 @@ __device__ __forceinline__ u32x4 settle(TileWeights& t, float c, float& m, float
                pack_f16(t.p[6], t.p[7])};
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void extend_attn_kernel(ExtendArgs a) {
+template <int D, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(Build<kWaves>::kPerSimd, Build<kWaves>::kPerSimd)))
+void extend_attn_kernel(ExtendArgs a) {
   constexpr int KB = D / 32;
   constexpr int JB = D / 16;
-  constexpr int TE = Tiles<D>::kElems;
-  constexpr int NC = Tiles<D>::kWaveChunks;
+  constexpr int kStageWaves = Build<kWaves>::kStageWaves;
+  constexpr int kAhead = Build<kWaves>::kAhead;
+  constexpr int TE = Tiles<D, kStageWaves>::kElems;
+  constexpr int NC = Tiles<D, kStageWaves>::kWaveChunks;
   constexpr int kWaveRows = 16 * kRowTiles;
-  // [buffer][step of the interval][K page 0 | K page 1 | V of both pages, interleaved]
-  __shared__ __attribute__((aligned(16))) uint16_t lds[2][kSub][4 * TE];
+  // [buffer][K page 0 | K page 1 | V of both pages, interleaved]
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2][4 * TE];
 
   const const_i32_ptr item = as_constant(a.items) + size_t(blockIdx.x) * kItemInts;
   const int seq = item[0];
   const int kvh = item[1];
-  const int t0 = item[2];
   const int nt = item[3];
+  // Whole items: steps [0, item[6]) of the block that starts at new token
+  // item[2]. Parts of items (kExtendPart*): steps [item[2], item[6]), with the
+  // block's first position and first query row in place of the sequence's.
+  const int t0 = a.parts ? 0 : item[2];
+  const int begin = a.parts ? item[2] : 0;
   const int prefix = item[4];
   const int qrow0 = item[5];
   const int nsteps = item[6];
+  const int slot = a.parts ? item[7] - 1 : -1;
   const int g = a.group;
   const int rows = nt * g;
   const int kend = prefix + t0 + nt;          // keys [0, kend) are read
@@ -270,18 +299,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
     lsum[rt] = 0.f;
   }
 
-  // Staging: wave w < 8 moves tile w / 2 of each step (0: K of the step's
-  // first page, 1: K of its second, 2 and 3: V of the two pages), in 1 KiB
-  // chunks (w % 2) * NC .. + NC - 1; waves 8 .. 11 stage nothing. The tile and
-  // its page are wave-uniform, so the global address is a scalar base plus a
-  // fixed per-lane offset, and every LDS address is fixed per lane: no
-  // per-step address arithmetic. A page past the item's last is replaced by
-  // its first page (always in range); its keys lie past kend and are masked.
-  // The keys are walked in intervals of kSub steps with one barrier each (one
-  // step: two would need prefetch registers that the three-waves-per-SIMD
-  // budget does not have).
+  // Staging: of the kStageWaves staging waves, kStageWaves / 4 move each tile
+  // of a step (0: K of the step's first page, 1: K of its second, 2 and 3: V
+  // of the two pages), NC chunks of 1 KiB each. The tile and its page are
+  // wave-uniform, so the global address is a scalar base plus a fixed per-lane
+  // offset, and every LDS address is fixed per lane: no per-step address
+  // arithmetic. A page past the item's last is replaced by its first page
+  // (always in range); its keys lie past kend and are masked. One step per
+  // barrier (two would need prefetch registers that three waves per SIMD do
+  // not have).
+  constexpr int kPerTile = kStageWaves / 4;
   const bool stager = wave < kStageWaves;
-  const int stile = (stager ? wave : 0) >> 1;
+  const int stile = (stager ? wave : 0) / kPerTile;
   const uint16_t* const spool = stile < 2 ? a.k_pool : a.v_pool;
   int soff[NC];    // element offset of this lane's piece in the tile
   int sdst0[NC];   // LDS element offset of the piece (K) or of its first 8-byte half (V)
@@ -289,7 +318,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
   int skey[NC];    // V: first token of the piece within the step's 32 keys
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    soff[q] = (((wave & 1) * NC + q) * 64 + lane) * 8;
+    soff[q] = (((wave % kPerTile) * NC + q) * 64 + lane) * 8;
     if (stile < 2) {
       sdst0[q] = stile * TE + soff[q];
       sdst1[q] = 0;
@@ -305,52 +334,43 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
       skey[q] = pg * kPage + 8 * c;
     }
   }
-  u32x4 pre[kSub][NC];
-  auto fetch = [&](int j) {
+  u32x4 pre[kAhead][NC];
+  auto fetch = [&](u32x4* x, int js) {
+    if (js >= nsteps) return;
+    const int pg0 = 2 * js;
+    const int p0 = bt[pg0];
+    const int page = (stile & 1) && pg0 + 1 < npages ? bt[pg0 + 1] : p0;
+    const uint16_t* src = spool + tile_base(page, a.num_kv_heads, kvh, D);
 #pragma unroll
-    for (int u = 0; u < kSub; ++u) {
-      const int js = kSub * j + u;
-      if (js >= nsteps) break;
-      const int pg0 = 2 * js;
-      const int p0 = bt[pg0];
-      const int page = (stile & 1) && pg0 + 1 < npages ? bt[pg0 + 1] : p0;
-      const uint16_t* src = spool + tile_base(page, a.num_kv_heads, kvh, D);
-#pragma unroll
-      for (int q = 0; q < NC; ++q) pre[u][q] = *reinterpret_cast<const u32x4*>(src + soff[q]);
-    }
+    for (int q = 0; q < NC; ++q) x[q] = *reinterpret_cast<const u32x4*>(src + soff[q]);
   };
-  // Writes the fetched pieces of interval j into LDS buffer `base` (one per
-  // step of the interval). V pieces are widened to fp16 and split into their
-  // two token quads (8 bytes each) at their interleaved slots; in the step
-  // that reaches kend, V tokens at or past it are zeroed first (they may be
-  // stale or NaN, and a zero weight times NaN is still NaN).
-  auto stage = [&](uint16_t (*base)[4 * TE], int j) {
+  // Writes the fetched pieces of step js into LDS buffer L. V pieces are
+  // widened to fp16 and split into their two token quads (8 bytes each) at
+  // their interleaved slots; in the step that reaches kend, V tokens at or
+  // past it are zeroed first (they may be stale or NaN, and a zero weight
+  // times NaN is still NaN).
+  auto stage = [&](uint16_t* L, const u32x4* px, int js) {
+    if (js >= nsteps) return;
+    if (stile < 2) {
 #pragma unroll
-    for (int u = 0; u < kSub; ++u) {
-      const int js = kSub * j + u;
-      if (js >= nsteps) break;
-      uint16_t* L = base[u];
-      if (stile < 2) {
+      for (int q = 0; q < NC; ++q) *reinterpret_cast<u32x4*>(L + sdst0[q]) = px[q];
+    } else {
+      const int key0 = js * kStepKeys;
+      const bool tail = key0 + kStepKeys > kend;
 #pragma unroll
-        for (int q = 0; q < NC; ++q) *reinterpret_cast<u32x4*>(L + sdst0[q]) = pre[u][q];
-      } else {
-        const int key0 = js * kStepKeys;
-        const bool tail = key0 + kStepKeys > kend;
+      for (int q = 0; q < NC; ++q) {
+        u32x4 x = px[q];
+        if (tail) {
 #pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          u32x4 x = pre[u][q];
-          if (tail) {
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-              const int key = key0 + skey[q] + 2 * w;
-              x[w] &= (key < kend ? 0x0000FFFFu : 0u) | (key + 1 < kend ? 0xFFFF0000u : 0u);
-            }
+          for (int w = 0; w < 4; ++w) {
+            const int key = key0 + skey[q] + 2 * w;
+            x[w] &= (key < kend ? 0x0000FFFFu : 0u) | (key + 1 < kend ? 0xFFFF0000u : 0u);
           }
-#pragma unroll
-          for (int w = 0; w < 4; ++w) x[w] = bf16x2_to_f16x2(x[w]);
-          *reinterpret_cast<u32x2*>(L + sdst0[q]) = u32x2{x[0], x[1]};
-          *reinterpret_cast<u32x2*>(L + sdst1[q]) = u32x2{x[2], x[3]};
         }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) x[w] = bf16x2_to_f16x2(x[w]);
+        *reinterpret_cast<u32x2*>(L + sdst0[q]) = u32x2{x[0], x[1]};
+        *reinterpret_cast<u32x2*>(L + sdst1[q]) = u32x2{x[2], x[3]};
       }
     }
   };
@@ -398,29 +418,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
       tail(std::false_type{});
   };
 
-  const int nint = (nsteps + kSub - 1) / kSub;
   if (stager) {
-    fetch(0);
-    stage(lds[0], 0);
+    fetch(pre[0], begin);
+    if constexpr (kAhead == 2) fetch(pre[1], begin + 1);
+    stage(lds[0], pre[0], begin);
   }
   __syncthreads();
 
-  // One interval from buffer `cur` while the next is staged into `nxt`; the
-  // loop is unrolled by two so that both buffers' addresses are constants.
-  auto interval = [&](int j, uint16_t (*cur)[4 * TE], uint16_t (*nxt)[4 * TE]) {
-    if (stager && j + 1 < nint) fetch(j + 1);
-#pragma unroll
-    for (int u = 0; u < kSub; ++u) {
-      const int js = kSub * j + u;
-      const int key0 = js * kStepKeys;
-      if (js < nsteps && key0 <= wave_kmax) compute(cur[u], key0);
-    }
-    if (stager && j + 1 < nint) stage(nxt, j + 1);
+  // One step from buffer `cur` while the next is staged into `nxt` and, two
+  // ahead, the one after it is fetched; the loop is unrolled by two so that
+  // both buffers' addresses (and prefetch registers) are constants.
+  auto interval = [&](int js, const uint16_t* cur, uint16_t* nxt, u32x4* fetched, u32x4* next) {
+    if (stager) fetch(fetched, js + kAhead);
+    if (js * kStepKeys <= wave_kmax) compute(cur, js * kStepKeys);
+    if (stager) stage(nxt, next, js + 1);
     __syncthreads();
   };
-  for (int j = 0; j < nint; j += 2) {
-    interval(j, lds[0], lds[1]);
-    if (j + 1 < nint) interval(j + 1, lds[1], lds[0]);
+  for (int js = begin; js < nsteps; js += 2) {
+    interval(js, lds[0], lds[1], pre[0], pre[kAhead - 1]);
+    if (js + 1 < nsteps) interval(js + 1, lds[1], lds[0], pre[kAhead - 1], pre[0]);
   }
 
   // Lane holds O[row col][16*jb + 4*grp + i] of each row tile.
@@ -433,12 +449,60 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
     const int tok = r / g;
     const int head = kvh * g + (r - tok * g);
     const size_t orow = size_t(qrow0 + t0 + tok) * a.num_q_heads + head;
-    const float inv = 1.f / lt;
-    float* dst = a.out + orow * D + 4 * grp;
+    // A part's result goes to its partial slot, with its lse in log2 units
+    // (o = 0 and lse = -inf for a row with no key in the part).
+    const float inv = slot >= 0 && lt == 0.f ? 0.f : 1.f / lt;
+    float* dst = (slot >= 0 ? a.part_o + (size_t(slot) * (kWaves * kWaveRows) + r) * D : a.out + orow * D) + 4 * grp;
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) *reinterpret_cast<f32x4*>(dst + 16 * jb) = o[rt][jb] * inv;
-    if (a.lse && grp == 0) a.lse[orow] = (m[rt] + __log2f(lt)) * kLn2;
+    if (grp != 0) continue;
+    if (slot >= 0)
+      a.part_lse[size_t(slot) * (kWaves * kWaveRows) + r] = m[rt] + __log2f(lt);
+    else if (a.lse)
+      a.lse[orow] = (m[rt] + __log2f(lt)) * kLn2;
   }
+}
+
+// Merges the parts of cut items (which items are cut and why: the cost rule of
+// the runner's plan): one block per item and kMergeThreads / (D / 4)
+// of its rows, one thread per row and 4 dims. Row of the merge list: first
+// slot, parts, tokens, first query row, KV head. Bound by the partial results'
+// bytes (every part writes and this launch reads D + 1 floats per row).
+constexpr int kMergeThreads = 256;
+
+template <int D>
+__global__ __launch_bounds__(kMergeThreads) void extend_merge_kernel(ExtendArgs a) {
+  constexpr int kLanes = D / 4;
+  const const_i32_ptr row = as_constant(a.merge_rows) + size_t(blockIdx.x) * kItemInts;
+  const int base = row[0];
+  const int n = row[1];
+  const int nt = row[2];
+  const int qrow = row[3];
+  const int kvh = row[4];
+  const int g = a.group;
+  const int r = int(blockIdx.y) * (kMergeThreads / kLanes) + int(threadIdx.x) / kLanes;
+  const int d4 = int(threadIdx.x) % kLanes;
+  if (r >= nt * g) return;
+  const float* lse_r = a.part_lse + size_t(base) * a.part_rows + r;
+  const float* o_r = a.part_o + (size_t(base) * a.part_rows + r) * D + 4 * d4;
+  float mx = -__builtin_inff(), wsum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int c = 0; c < n; ++c) {
+    const float l = lse_r[size_t(c) * a.part_rows];
+    const f32x4 o = *reinterpret_cast<const f32x4*>(o_r + size_t(c) * a.part_rows * D);
+    const float mnew = fmaxf(mx, l);
+    const float mref = mnew == -__builtin_inff() ? 0.f : mnew;
+    const float keep = __builtin_amdgcn_exp2f(mx - mref);
+    const float w = __builtin_amdgcn_exp2f(l - mref);
+    acc = acc * keep + o * w;
+    wsum = wsum * keep + w;
+    mx = mnew;
+  }
+  const int tok = r / g;
+  const size_t orow = size_t(qrow + tok) * a.num_q_heads + kvh * g + (r - tok * g);
+  *reinterpret_cast<f32x4*>(a.out + orow * D + 4 * d4) = acc * (1.f / wsum);
+  if (a.lse && d4 == 0) a.lse[orow] = (mx + __log2f(wsum)) * kLn2;
 }
 
 // Stores the new tokens' keys and values of one item (one sequence and KV
@@ -496,24 +560,120 @@ __global__ __launch_bounds__(kStoreThreads) void kv_store_kernel(ExtendArgs a) {
   }
 }
 
+// The same store, a page at a time (sf_runner_extend; full re-prefill of 95k
+// tokens 125 -> 99 us, 4 x 256 tokens 11.4 -> 9 us, where items of 54 tokens
+// left most pages to slot-by-slot value stores): a row of the store
+// list names a run of pages of one sequence that new tokens land in (seq,
+// first page, pages, first new position, end position, query row of the first
+// new position), and each wave takes (page, KV head) tiles of it. Bound by
+// memory; the tile's 4 KiB (D = 128) go out as whole 1 KiB key rows and 64
+// contiguous bytes of values per lane (two dims of all slots, transposed in
+// registers from 4-byte loads); only a page the new tokens do not fill takes
+// slot-by-slot stores. The launch also copies the attention launch's rows
+// from pinned host memory (a.copy_*), so that those workgroups start from
+// device memory.
+template <int D>
+__global__ __launch_bounds__(kStoreThreads) void kv_store_pages_kernel(ExtendArgs a) {
+  const int stride = int(gridDim.x) * kStoreThreads;
+  int i0 = int(blockIdx.x) * kStoreThreads + int(threadIdx.x);
+  const int copied = i0 < a.copy_ints ? a.copy_src[i0] : 0;
+
+  const const_i32_ptr row = as_constant(a.store_rows) + size_t(blockIdx.x) * kItemInts;
+  const int seq = row[0];
+  const int pb = row[1];
+  const int np = row[2];
+  const int first = row[3];
+  const int end = row[4];
+  const int qrow = row[5];
+  const const_i32_ptr bt = as_constant(a.block_table) + size_t(seq) * a.bt_stride;
+  const int lane = int(threadIdx.x) & 63;
+  const int hkv = a.num_kv_heads;
+  const size_t tok_stride = size_t(hkv) * D;
+  for (int i = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6); i < np * hkv; i += kStoreThreads / 64) {
+    const int pg = pb + i / hkv;
+    const int kvh = i % hkv;
+    const int lo = max(first, pg * kPage), hi = min(end, (pg + 1) * kPage);   // positions stored
+    const size_t tile = tile_base(bt[pg], hkv, kvh, D);
+    // new-token row of position lo; slot s of the page is row s - lo % kPage
+    const uint16_t* kn = a.k_new + size_t(qrow + (lo - first)) * tok_stride + size_t(kvh) * D;
+    const uint16_t* vn = a.v_new + size_t(qrow + (lo - first)) * tok_stride + size_t(kvh) * D;
+    const int s0 = lo % kPage, s1 = s0 + (hi - lo);
+    {
+      const int s = lane & 15;
+      const bool ok = s >= s0 && s < s1;
+#pragma unroll
+      for (int j = 0; j < D / 32; ++j) {
+        const int c = 4 * j + (lane >> 4);
+        if (ok)
+          *reinterpret_cast<u32x4*>(a.k_dst + tile + (c * kPage + s) * 8) =
+              *reinterpret_cast<const u32x4*>(kn + size_t(s - s0) * tok_stride + 8 * c);
+      }
+    }
+    uint16_t* dst = a.v_dst + tile;
+    const int dim = 2 * (lane % (D / 2));   // this lane's two dims (D = 64: of 8 of the 16 slots)
+    if (hi - lo == kPage) {
+      constexpr int kHalves = D / 64;
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) {
+        const int t0 = 8 * (D == 64 ? lane / 32 : h);
+        uint32_t x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const uint32_t*>(vn + size_t(t0 + e) * tok_stride + dim);
+        u32x4 d0, d1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          d0[e] = (x[2 * e] & 0xFFFFu) | (x[2 * e + 1] << 16);
+          d1[e] = (x[2 * e] >> 16) | (x[2 * e + 1] & 0xFFFF0000u);
+        }
+        *reinterpret_cast<u32x4*>(dst + dim * kPage + t0) = d0;
+        *reinterpret_cast<u32x4*>(dst + (dim + 1) * kPage + t0) = d1;
+      }
+    } else if (lane < D / 2) {
+      for (int s = s0; s < s1; ++s) {
+        const uint32_t x = *reinterpret_cast<const uint32_t*>(vn + size_t(s - s0) * tok_stride + dim);
+        dst[dim * kPage + s] = uint16_t(x);
+        dst[(dim + 1) * kPage + s] = uint16_t(x >> 16);
+      }
+    }
+  }
+  if (i0 < a.copy_ints) a.copy_dst[i0] = copied;
+  for (i0 += stride; i0 < a.copy_ints; i0 += stride) a.copy_dst[i0] = a.copy_src[i0];
+}
+
+// Copies the attention launch's rows when there is no store launch to do it.
+__global__ __launch_bounds__(kStoreThreads) void extend_rows_kernel(ExtendArgs a) {
+  const int i = int(blockIdx.x) * kStoreThreads + int(threadIdx.x);
+  if (i < a.copy_ints) a.copy_dst[i] = a.copy_src[i];
+}
+
 }  // namespace
+
+template <int D>
+hipError_t launch_extend_d(const ExtendArgs& a, hipStream_t stream) {
+  if (a.num_store > 0) {
+    hipLaunchKernelGGL(kv_store_pages_kernel<D>, dim3(a.num_store), dim3(kStoreThreads), 0, stream, a);
+  } else if (a.k_new) {
+    hipLaunchKernelGGL(kv_store_kernel<D>, dim3(a.num_items), dim3(kStoreThreads), 0, stream, a);
+  } else if (a.copy_ints > 0) {
+    hipLaunchKernelGGL(extend_rows_kernel, dim3((a.copy_ints + kStoreThreads - 1) / kStoreThreads),
+                       dim3(kStoreThreads), 0, stream, a);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (a.parts && a.part_rows == kExtendSmallRows)
+    hipLaunchKernelGGL((extend_attn_kernel<D, 4>), dim3(a.num_items), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((extend_attn_kernel<D, 12>), dim3(a.num_items), dim3(768), 0, stream, a);
+  if ((e = hipGetLastError()) != hipSuccess || a.num_merge == 0) return e;
+  constexpr int kRowsPerBlock = kMergeThreads / (D / 4);
+  hipLaunchKernelGGL(extend_merge_kernel<D>, dim3(a.num_merge, (a.part_rows + kRowsPerBlock - 1) / kRowsPerBlock),
+                     dim3(kMergeThreads), 0, stream, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream) {
   if (a.num_items == 0) return hipSuccess;
-  const dim3 grid(a.num_items), block(kThreads);
-  if (a.k_new) {
-    if (a.head_dim == 128)
-      hipLaunchKernelGGL(kv_store_kernel<128>, grid, dim3(kStoreThreads), 0, stream, a);
-    else
-      hipLaunchKernelGGL(kv_store_kernel<64>, grid, dim3(kStoreThreads), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (a.head_dim == 128)
-    hipLaunchKernelGGL(extend_attn_kernel<128>, grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL(extend_attn_kernel<64>, grid, block, 0, stream, a);
-  return hipGetLastError();
+  return a.head_dim == 128 ? launch_extend_d<128>(a, stream) : launch_extend_d<64>(a, stream);
 }
 
 }  // namespace sf

@@ -25,6 +25,7 @@
 
 #include "sf_internal.h"
 
+static_assert(sizeof(sf_runner_memory) == 56, "sf_runner_memory layout is part of the ABI");
 static_assert(sizeof(sf_runner_extras) == 56, "sf_runner_extras layout is part of the ABI");
 
 namespace {
@@ -33,6 +34,9 @@ constexpr int kRing = 32;
 constexpr int kMarkEvery = 16;
 constexpr int kMarks = 4;
 constexpr int kFp8WorkersPerCu = 8;
+// Without a store launch to copy the rows, a copy launch (about 4 us) pays from
+// about two rounds of workgroups on, each starting with a read over PCIe.
+constexpr int kExtendCopyParts = 512;
 static_assert(kMarkEvery < kRing, "a slot's last step must be marked before the slot comes round again");
 
 struct Pinned {
@@ -50,6 +54,19 @@ struct Mark {
   bool valid = false;
 };
 
+// Memory lent by sf_runner_extend's caller.
+struct Lent {
+  void* pinned = nullptr;
+  const char* pinned_dev = nullptr;   // the same memory as the kernels address it
+  int32_t slots = 0;
+  uint64_t slot_bytes = 0;
+  void* device = nullptr;
+  uint64_t device_bytes = 0;
+  uint64_t next = 0;                  // slots go round
+  uint64_t last_step[kRing] = {};     // the step that last read the slot
+  bool used[kRing] = {};
+};
+
 }  // namespace
 
 struct sf_runner {
@@ -63,6 +80,7 @@ struct sf_runner {
   hipStream_t last_stream = nullptr;
   void* workspace = nullptr;
   uint64_t workspace_bytes = 0;
+  Lent lent;
   uint64_t steps = 0;
   sf_plan_info last;
 };
@@ -140,6 +158,23 @@ sf_status grow_device(sf_runner* r, void** ptr, uint64_t* have, uint64_t bytes, 
   if (hipMalloc(ptr, want) != hipSuccess) return SF_ERR_HIP;
   *have = want;
   return SF_OK;
+}
+
+// Counts a step whose launches (status st) may read its slot, and marks the
+// steps in their turn.
+sf_status finish_step(sf_runner* r, hipStream_t main, sf_status st, uint64_t mark_every) {
+  r->last_stream = main;
+  ++r->steps;
+  if (r->steps - r->unmarked >= mark_every && mark_steps(r) != SF_OK) {
+    // Without the mark nothing orders a later rewrite of these slots after
+    // the steps' reads: wait for the stream instead.
+    (void)hipStreamSynchronize(main);
+    for (auto& p : r->ring) p.used = false;
+    for (auto& u : r->lent.used) u = false;
+    r->unmarked = r->steps;
+    if (st == SF_OK) st = SF_ERR_HIP;
+  }
+  return st;
 }
 
 }  // namespace
@@ -293,17 +328,107 @@ extern "C" sf_status sf_runner_step(sf_runner* r, const sf_attn_desc* desc, cons
   }
   pin.used = true;
   pin.last_step = r->steps;
-  r->last_stream = main;
-  ++r->steps;
-  if (r->steps - r->unmarked >= kMarkEvery && mark_steps(r) != SF_OK) {
-    // Without the mark nothing orders a later rewrite of these slots after
-    // the steps' reads: wait for the stream instead.
-    (void)hipStreamSynchronize(main);
-    for (auto& p : r->ring) p.used = false;
-    r->unmarked = r->steps;
-    if (st == SF_OK) st = SF_ERR_HIP;
+  return finish_step(r, main, st, kMarkEvery);
+}
+
+// Extend attention, in memory that the caller lends: the pinned part is cut
+// into slots that the plans go round, the device part is the workspace.
+extern "C" sf_status sf_runner_extend(sf_runner* r, const sf_attn_desc* desc, const int32_t* seq_lens_host,
+                                      const int32_t* q_lens_host, const void* q, const void* k_new,
+                                      const void* v_new, void* k_pool, void* v_pool, const int32_t* block_table,
+                                      float* out, float* lse, sf_runner_memory* memory, void* stream,
+                                      sf_extend_info* info_out) {
+  if (!r || !desc || !info_out || !memory) return SF_ERR_INVALID_ARG;
+  if (desc->num_q_heads != r->shape.num_q_heads || desc->num_kv_heads != r->shape.num_kv_heads ||
+      desc->head_dim != r->shape.head_dim || desc->page_size != r->shape.page_size)
+    return SF_ERR_INVALID_ARG;
+  if ((reinterpret_cast<uintptr_t>(memory->pinned) | reinterpret_cast<uintptr_t>(memory->device)) & 15u)
+    return SF_ERR_INVALID_ARG;
+  hipStream_t main = static_cast<hipStream_t>(stream);
+  // Slots are reused by waiting for events on the host, which a graph's
+  // replays would not: a capturing stream is left to sf_extend_attn.
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(main, &capturing) != hipSuccess) return SF_ERR_HIP;
+  if (capturing != hipStreamCaptureStatusNone) return SF_ERR_UNSUPPORTED;
+
+  // Other memory than the last call's: nothing may still use either.
+  sf_status st = SF_OK;
+  Lent& lent = r->lent;
+  const uint64_t slot_bytes = memory->slots > 0 ? memory->pinned_bytes / memory->slots / 32 * 32 : 0;
+  if (lent.pinned != memory->pinned || lent.slots != memory->slots || lent.slot_bytes != slot_bytes ||
+      lent.device != memory->device || lent.device_bytes != memory->device_bytes) {
+    if ((st = wait_all(r)) != SF_OK) return st;
+    if (memory->slots < 0 || memory->slots > kRing || (memory->pinned == nullptr) != (memory->slots == 0))
+      return SF_ERR_INVALID_ARG;
+    void* dev = nullptr;
+    if (memory->pinned && hipHostGetDevicePointer(&dev, memory->pinned, 0) != hipSuccess) return SF_ERR_HIP;
+    lent = Lent{};
+    lent.pinned = memory->pinned;
+    lent.pinned_dev = static_cast<const char*>(dev);
+    lent.slots = memory->slots;
+    lent.slot_bytes = slot_bytes;
+    lent.device = memory->device;
+    lent.device_bytes = memory->device_bytes;
   }
-  return st;
+  const int slot = lent.slots > 0 ? lent.next % lent.slots : 0;
+  if (lent.used[slot] && (st = wait_step(r, lent.last_step[slot])) != SF_OK) return st;
+  lent.used[slot] = false;
+
+  const bool store = k_new != nullptr;
+  sf::ExtendPlan plan;
+  try {
+    int32_t* work = reinterpret_cast<int32_t*>(static_cast<char*>(lent.pinned) + uint64_t(slot) * lent.slot_bytes);
+    st = sf::extend_plan_parts(desc, seq_lens_host, q_lens_host, r->opts.num_cus, store, work, lent.slot_bytes,
+                               &plan, info_out);
+  } catch (const std::bad_alloc&) {
+    return SF_ERR_HIP;
+  }
+  if (st != SF_OK && st != SF_ERR_CAPACITY) return st;
+  // Device memory: partial results, then the device copy of the part and
+  // merge rows. The store launch makes that copy, or a launch of its own where
+  // enough workgroups would otherwise read their row over PCIe.
+  const uint64_t row_ints = (uint64_t(plan.num_parts) + plan.num_merge) * sf::kItemInts;
+  if (row_ints > INT32_MAX) return SF_ERR_INVALID_ARG;
+  const uint64_t lse_off = sf::align256(uint64_t(plan.num_slots) * plan.rows * desc->head_dim * 4);
+  const uint64_t rows_off = lse_off + sf::align256(uint64_t(plan.num_slots) * plan.rows * 4);
+  const bool copy = store || plan.num_parts > kExtendCopyParts;
+  const uint64_t device_bytes = rows_off + (copy ? row_ints * 4 : 0);
+  if (st == SF_ERR_CAPACITY || lent.device_bytes < device_bytes) {
+    memory->need_slot = plan.bytes();
+    memory->need_device = device_bytes;
+    return SF_ERR_CAPACITY;
+  }
+  if (plan.num_parts == 0) return SF_OK;
+  const int32_t* work_dev = reinterpret_cast<const int32_t*>(lent.pinned_dev + uint64_t(slot) * lent.slot_bytes);
+  sf::ExtendArgs a;
+  if ((st = sf::extend_args(desc, work_dev, q, k_new, v_new, k_pool, v_pool, block_table, out, lse, &a)) != SF_OK)
+    return st;
+  // Steps of another stream may still use the device memory: they are waited
+  // for (steps on one stream are in order by themselves).
+  if (r->steps > 0 && main != r->last_stream && (st = wait_all(r)) != SF_OK) return st;
+  char* ws = static_cast<char*>(lent.device);
+  a.parts = true;
+  a.num_items = plan.num_parts;
+  a.part_rows = plan.rows;
+  a.part_o = reinterpret_cast<float*>(ws);
+  a.part_lse = reinterpret_cast<float*>(ws + lse_off);
+  a.num_merge = plan.num_merge;
+  a.num_store = plan.num_store;
+  a.store_rows = work_dev + row_ints;
+  if (copy) {
+    a.copy_src = work_dev;
+    a.copy_dst = reinterpret_cast<int32_t*>(ws + rows_off);
+    a.copy_ints = int32_t(row_ints);
+    a.items = a.copy_dst;
+  }
+  a.merge_rows = a.items + int64_t(plan.num_parts) * sf::kItemInts;
+  st = sf::launch_extend(a, main) == hipSuccess ? SF_OK : SF_ERR_HIP;
+  lent.used[slot] = true;
+  lent.last_step[slot] = r->steps;
+  ++lent.next;
+  // every half round of slots is marked, so a slot's last step is marked
+  // before the slot comes round again
+  return finish_step(r, main, st, lent.slots > 1 ? lent.slots / 2 : 1);
 }
 
 extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, uint64_t work_bytes,

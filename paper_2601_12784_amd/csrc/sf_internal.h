@@ -163,10 +163,50 @@ struct ExtendArgs {
   const uint16_t* v_new;
   uint16_t* k_dst;            // the pools, writable
   uint16_t* v_dst;
+  // sf_runner_extend: items are parts of key walks (ExtendPlan), the partial
+  // results of cut walks are merged by a launch of their own, and the store
+  // goes by pages. All zero / NULL for sf_extend_attn.
+  bool parts;
+  int32_t part_rows;          // rows of an item: kExtendRows or kExtendSmallRows
+  float* part_o;              // [slots][part_rows][D]
+  float* part_lse;            // [slots][part_rows], log2 units
+  const int32_t* merge_rows;
+  int32_t num_merge;
+  const int32_t* store_rows;
+  int32_t num_store;
+  const int32_t* copy_src;    // the part and merge rows in pinned host memory
+  int32_t* copy_dst;          // and their device copy
+  int32_t copy_ints;
 };
 
-// Rows (tokens x query heads of a group) of one extend work item.
+// Rows (tokens x query heads of a group) of one extend work item: of the plan
+// of sf_extend_attn_plan, and of the small items that sf_runner_extend's plan
+// takes where the large ones would leave compute units idle.
 constexpr int kExtendRows = 384;
+constexpr int kExtendSmallRows = 128;
+
+// The plan of sf_runner_extend: rows of kItemInts ints, in this order.
+//   parts: seq, kv_head, first step, tokens, position of the item's first
+//     token, its query row, end step, partial slot + 1 (0: written to out);
+//     longest first
+//   merges: first slot, parts, tokens, first query row, kv_head
+//   stores: seq, first page, pages, first new position, end position, query
+//     row of the first new position
+struct ExtendPlan {
+  int32_t rows;               // kExtendRows or kExtendSmallRows
+  int32_t num_parts, num_merge, num_store, num_slots;
+  uint64_t bytes() const { return (uint64_t(num_parts) + num_merge + num_store) * kItemInts * 4; }
+};
+// Plans into work (capacity bytes; SF_ERR_CAPACITY if too small, *plan then
+// holds the sizes). info: what sf_extend_attn_plan reports for the same call.
+sf_status extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_lens_host, const int32_t* q_lens_host,
+                            int32_t num_cus, bool store, int32_t* work, uint64_t capacity, ExtendPlan* plan,
+                            sf_extend_info* info);
+
+// Argument checks and launch arguments that both extend entry points share.
+sf_status extend_args(const sf_attn_desc* desc, const int32_t* work_dev, const void* q, const void* k_new,
+                      const void* v_new, void* k_pool, void* v_pool, const int32_t* block_table, float* out,
+                      float* lse, ExtendArgs* args);
 
 // start / stop (hipEvent_t, may be NULL) take the kernel's own start and end
 // times: the launch records them from its dispatch (hipExtLaunchKernel), so

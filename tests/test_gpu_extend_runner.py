@@ -1,0 +1,125 @@
+"""Extend attention through the runner where its plan differs from the plain
+one: key walks cut into parts, 128-row items, the page-wise store, and calls
+that queue up behind each other. Against the fp64 oracle at
+|gpu - ref| <= 2e-3 + 1e-2 |ref|; stores bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_12784_amd import binding as B
+from paper_2601_12784_amd.workloads import bf16_bits, build_extend
+from test_gpu_extend import assert_close, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+CASES = {
+    # few rows after long prefixes: 128-row items, walks cut into many parts; a diagonal that starts inside a part
+    "long_walks": ([5000, 33, 2050], [3, 1, 40]),
+    # parts in which the first rows of a block see no key at all
+    "diagonal": ([1500], [1500]),
+    # 384-row items cut, one sequence with no new tokens
+    "large_cut": ([3000, 2900, 40, 3100], [260, 200, 0, 300]),
+    # parts that end in a ragged page, with a block of one token
+    "ragged": ([1999, 2001, 1985], [129, 56, 1]),
+}
+
+
+@pytest.mark.parametrize("store", [False, True])
+@pytest.mark.parametrize("case", sorted(CASES))
+@pytest.mark.parametrize("shape", [(28, 4, 128), (16, 1, 128), (3, 3, 64), (8, 2, 64)], ids=lambda s: "x".join(map(str, s)))
+def test_runner_plan_matches_oracle(shape, case, store):
+    hq, hkv, d = shape
+    lens, qls = CASES[case]
+    print(f"extend runner {case} {shape} store={store}", flush=True)
+    eb = build_extend(lens, qls, hq, hkv, d, seed=41 + len(case) + hq, k_mult=2.0)
+    k0, v0 = bf16_bits(eb.batch.k_pool).copy(), bf16_bits(eb.batch.v_pool).copy()
+    kp = vp = None
+    if store:   # the new tokens' slots hold NaN until the store writes them
+        pages, slots = eb.slots()
+        kh, vh = k0.copy(), v0.copy()
+        kh[pages, :, :, slots, :] = 0x7FC0
+        vh[pages, :, :, slots] = 0x7FC0
+        kp, vp = (torch.from_numpy(x.view(np.int16)).view(torch.bfloat16) for x in (kh, vh))
+    out, lse, k1, v1, _ = run_gpu(eb, store=store, k_pool=kp, v_pool=vp)
+    assert np.array_equal(bf16_bits(k1), k0) and np.array_equal(bf16_bits(v1), v0)
+    assert_close(out, lse, run_oracle(eb), f"{case} {shape}")
+
+
+def test_runner_agrees_with_the_plain_entry_point():
+    """The same call through sf_extend_attn (whole 384-row items): the two
+    plans' results differ only by the merge's fp32 rounding."""
+    eb = build_extend([2600, 700], [300, 700], 28, 4, 128, seed=5)
+    b = eb.batch
+    out, lse, *_ = run_gpu(eb)
+    desc = B.make_desc(2, 28, 4, 128, b.block_table.shape[1], b.num_pages, b.scale)
+    info, work = B.sf_extend_attn_plan(desc, b.seq_lens, eb.q_lens)
+    o2 = torch.empty(out.shape, dtype=torch.float32, device="cuda")
+    l2 = torch.empty(lse.shape, dtype=torch.float32, device="cuda")
+    B.sf_extend_attn(desc, info, None, torch.from_numpy(work).cuda(), eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(),
+                     torch.from_numpy(b.block_table).cuda(), o2, l2)
+    torch.cuda.synchronize()
+    # softmax weights are fp16 relative to a part's own reference: 2^-11 each, averaged over the keys
+    assert float((o2.cpu() - torch.from_numpy(out)).norm() / o2.cpu().norm()) < 2.0 ** -11
+    assert np.allclose(l2.cpu().numpy(), lse, atol=1e-4)
+
+
+def test_queued_calls_with_growing_and_shrinking_plans():
+    """Calls queue up without a wait between them, on two streams in turn, with
+    plans that outgrow the lent memory and shrink again; each result is the
+    call's own, bit for bit."""
+    ebs = [build_extend(lens, qls, 28, 4, 128, seed=60 + i) for i, (lens, qls) in enumerate(
+        [([300], [20]), ([4000, 4100], [64, 100]), ([90, 17], [90, 1]), ([6000], [700]), ([500], [500])])]
+    data = []
+    for eb in ebs:
+        b = eb.batch
+        data.append((eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(),
+                     b.seq_lens, eb.q_lens, b.scale))
+    want = []
+    for x in data:
+        want.append(B.ExtendAttention(28, 4, 128)(*x))
+        torch.cuda.synchronize()
+    call = B.ExtendAttention(28, 4, 128)
+    side = torch.cuda.Stream()
+    outs = []
+    for i in range(60):
+        x = data[(i * 7 + i // 9) % len(data)]
+        out = torch.empty_like(want[(i * 7 + i // 9) % len(data)])
+        torch.cuda.synchronize() if i % 20 == 19 else None
+        outs.append(call(*x, out=out, stream=side if i // 10 % 2 else None))
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        assert torch.equal(out, want[(i * 7 + i // 9) % len(data)]), f"call {i}"
+
+
+def test_captured_stream_is_left_to_the_plain_entry_point():
+    """sf_runner_extend refuses a capturing stream before it launches or records
+    anything, so the capture goes on."""
+    call = B.ExtendAttention(8, 2, 64)
+    eb = build_extend([60], [60], 8, 2, 64, seed=2)
+    b = eb.batch
+    args = (eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda())
+    out = torch.empty((60, 8, 64), dtype=torch.float32, device="cuda")
+    call(*args, b.seq_lens, eb.q_lens, b.scale, out=out)
+    torch.cuda.synchronize()
+    desc = B.make_desc(1, 8, 2, 64, b.block_table.shape[1], b.num_pages, b.scale)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st = call._L.sf_runner_extend(call._runner, desc, b.seq_lens.ctypes.data, eb.q_lens.ctypes.data,
+                                      *(t.data_ptr() for t in args[:1]), None, None, *(t.data_ptr() for t in args[1:]),
+                                      out.data_ptr(), None, call._memory, torch.cuda.current_stream().cuda_stream,
+                                      B.sf_extend_info())
+        out.add_(1.0)
+    before = out.clone()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert st == B.UNSUPPORTED and torch.equal(out, before + 1.0)
