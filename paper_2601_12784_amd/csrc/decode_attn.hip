@@ -1025,6 +1025,120 @@ __device__ __forceinline__ void merge_row(const CombineArgs& a, int row) {
 
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) { merge_row(a, blockIdx.x); }
 
+// The merge of pairs cut into many segments (a few long sequences: 32768
+// tokens alone make 256 segments per pair). It is bound by memory latency, not
+// bytes (3.7 MB for that sequence). One workgroup per (pair, head): its slices
+// of D / 4 threads each take every kSlices-th segment, so kSlices (unrolled: 4
+// kSlices) segments are in flight at once where combine_kernel's single slice
+// takes a memory round trip per four; the slices are then merged through
+// registers and LDS. One sequence of 32768 tokens, 28/4 heads: 28.7 -> 3.8 us,
+// step 44.7 -> 21.7 us (1024 threads per workgroup took the same, and 10.6
+// against 5.4 us at four segments per pair). kAppend: the newest token joins
+// as in merge_append_kernel.
+constexpr int kWideThreads = 256;
+
+template <int D, bool kAppend>
+__device__ __forceinline__ void merge_wide(const CombineArgs& a, int index, int h) {
+  constexpr int kLanes = D / 4;                     // threads of a slice
+  constexpr int kSlices = kWideThreads / kLanes;
+  constexpr int kWavesWide = kWideThreads / 64;
+  __shared__ f32x4 acc_w[kWavesWide][kLanes];
+  __shared__ float max_w[kWavesWide], sum_w[kWavesWide];
+  __shared__ float z_new;
+  const const_i32_ptr row = as_constant(a.items) + size_t(index) * kItemInts;
+  const int seq = row[0];
+  const int kvh = row[1];
+  const int base = row[2];
+  const int n = row[3];
+  const int g = a.group;
+  const int d4 = int(threadIdx.x) % kLanes;
+  const int slice = int(threadIdx.x) / kLanes;
+  const int wave = int(threadIdx.x) >> 6;
+  const int head = kvh * g + h;
+  const size_t orow = size_t(seq) * a.num_q_heads + head;
+
+  // Maximum (log2 units), weight sum and weighted sum of this slice's
+  // segments. A slice may have none, and a segment no token (appending): a
+  // maximum of -inf is replaced by 0 in the exponents, which gives weight 0.
+  float mx = -__builtin_inff(), wsum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](float l, float w0, const f32x4& o) {
+    const float mnew = fmaxf(mx, l);
+    const float mref = mnew == -__builtin_inff() ? 0.f : mnew;
+    const float keep = fast_exp2(mx - mref);
+    const float w = fast_exp2(l - mref);
+    acc = acc * keep + o * w;
+    wsum = wsum * keep + w0 * w;
+    mx = mnew;
+  };
+  {
+    const float* lse_h = a.part_lse + size_t(base) * g + h;
+    const float* o_h = a.part_o + (size_t(base) * g + h) * D + 4 * d4;
+#pragma unroll 4
+    for (int c = slice; c < n; c += kSlices)
+      add(lse_h[size_t(c) * g], 1.f, *reinterpret_cast<const f32x4*>(o_h + size_t(c) * g * D));
+  }
+  if constexpr (kAppend) {
+    if (wave == 0) {   // the newest token's score: lanes 0 .. D / 8 - 1, 8 dims each
+      float z = 0.f;
+      const int part = lane_id();
+      if (part < D / 8) {
+        const u32x4 qv = load16(a.q + orow * D + 8 * part);
+        const u32x4 kv = load16(a.k_new + (size_t(seq) * a.num_kv_heads + kvh) * D + 8 * part);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          z += bf16_value(qv[e] & 0xFFFFu) * bf16_value(kv[e] & 0xFFFFu);
+          z += bf16_value(qv[e] >> 16) * bf16_value(kv[e] >> 16);
+        }
+      }
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) z += __shfl_xor(z, off);
+      if (part == 0) z_new = z * a.scale_log2;
+    }
+  }
+  // the slices of a wave, then the waves
+#pragma unroll
+  for (int off = kLanes; off < 64; off <<= 1) {
+    f32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(acc[i], off);
+    const float m2 = __shfl_xor(mx, off), w2 = __shfl_xor(wsum, off);
+    add(m2, w2, o);
+  }
+  if (lane_id() < kLanes) acc_w[wave][d4] = acc;
+  if (lane_id() == 0) {
+    max_w[wave] = mx;
+    sum_w[wave] = wsum;
+  }
+  __syncthreads();
+  if (int(threadIdx.x) < kLanes) {
+#pragma unroll
+    for (int w = 1; w < kWavesWide; ++w) add(max_w[w], sum_w[w], acc_w[w][d4]);
+    if constexpr (kAppend) {
+      const u32x2 vv = *reinterpret_cast<const u32x2*>(a.v_new + (size_t(seq) * a.num_kv_heads + kvh) * D + 4 * d4);
+      add(z_new, 1.f, f32x4{bf16_value(vv[0] & 0xFFFFu), bf16_value(vv[0] >> 16), bf16_value(vv[1] & 0xFFFFu),
+                            bf16_value(vv[1] >> 16)});
+    }
+    *reinterpret_cast<f32x4*>(a.out + orow * D + 4 * d4) = acc * (1.f / wsum);
+    if (a.lse && d4 == 0) a.lse[orow] = (mx + __log2f(wsum)) * kLn2;
+  }
+  if constexpr (kAppend) {
+    if (h == 0 && wave == 1) {   // store the token, once per pair
+      const int t = row[4] - 1;
+      const size_t entry = size_t(seq) * a.bt_stride + t / kPage;
+      const int fresh = a.new_pages ? as_constant(a.new_pages)[seq] : -1;
+      const int page = fresh >= 0 ? fresh : as_constant(a.block_table)[entry];
+      store_token<D>(a.k_dst, a.v_dst, a.k_new, a.v_new, a.num_kv_heads, seq, kvh, page, t % kPage, lane_id());
+      if (fresh >= 0 && kvh == 0 && lane_id() == 0) a.bt_dst[entry] = fresh;
+    }
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(kWideThreads) void combine_wide_kernel(CombineArgs a) {
+  merge_wide<D, false>(a, int(blockIdx.x), int(blockIdx.y));
+}
+
 // The merge launch of an appending step. The attention pass left each
 // sequence's newest token (index len - 1, not yet in the pool) out; here it
 // joins every (sequence, KV head) pair as one more term of the softmax:
@@ -1035,17 +1149,25 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) { merge_row
 // W relative to l = its maximum), or out, lse and W = 1 of a pair the
 // attention pass finished. Then the token is stored into its page slot, and
 // a page newly given to it is recorded in the block table (KV head 0).
-// Blocks [0, num_items) take the split pairs' merge rows; the rest take one
+// Blocks [0, num_items) take the split pairs' merge rows (kWide: blocks
+// [0, num_items * g), one per pair and head, by merge_wide); the rest take one
 // work item each (or one of single_rows, when given), acting on the
 // single-segment pairs.
-template <int D>
+template <int D, bool kWide>
 __global__ __launch_bounds__(256) void merge_append_kernel(CombineArgs a) {
+  static_assert(kWideThreads == 256, "both kinds of block in one launch");
+  const int block = int(blockIdx.x);
+  const int split_blocks = kWide ? a.num_items * a.group : a.num_items;
+  if (kWide && block < split_blocks) {
+    merge_wide<D, true>(a, block / a.group, block % a.group);
+    return;
+  }
   constexpr int kPerThread = (kMaxGroup * (D / 4) + 255) / 256;   // (head, 4 dims) items per thread, at most
   __shared__ float z_new[kMaxGroup];
-  const bool split = int(blockIdx.x) < a.num_items;
+  const bool split = !kWide && block < split_blocks;
   const const_i32_ptr rest = a.single_rows ? as_constant(a.single_rows) : as_constant(a.work_items);
-  const_i32_ptr row = split ? as_constant(a.items) + size_t(blockIdx.x) * kItemInts
-                            : rest + size_t(int(blockIdx.x) - a.num_items) * kItemInts;
+  const_i32_ptr row = split ? as_constant(a.items) + size_t(block) * kItemInts
+                            : rest + size_t(block - split_blocks) * kItemInts;
   const int seq = row[0];
   const int kvh = row[1];
   const int base = row[2];
@@ -1141,117 +1263,6 @@ __global__ __launch_bounds__(256) void merge_append_kernel(CombineArgs a) {
   }
 }
 
-// The merge of pairs cut into many segments (a few long sequences: 32768
-// tokens alone make 256 segments per pair). It is bound by memory latency, not
-// bytes (3.7 MB for that sequence). One workgroup per (pair, head): its slices
-// of D / 4 threads each take every kSlices-th segment, so kSlices (unrolled: 4
-// kSlices) segments are in flight at once where combine_kernel's single slice
-// takes a memory round trip per four; the slices are then merged through
-// registers and LDS. One sequence of 32768 tokens, 28/4 heads: 28.7 -> 3.8 us,
-// step 44.7 -> 21.7 us (1024 threads per workgroup took the same, and 10.6
-// against 5.4 us at four segments per pair). kAppend: the newest token joins
-// as in merge_append_kernel, whose launch then has only the single-segment
-// rows left.
-constexpr int kWideThreads = 256;
-
-template <int D, bool kAppend>
-__global__ __launch_bounds__(kWideThreads) void combine_wide_kernel(CombineArgs a) {
-  constexpr int kLanes = D / 4;                     // threads of a slice
-  constexpr int kSlices = kWideThreads / kLanes;
-  constexpr int kWavesWide = kWideThreads / 64;
-  __shared__ f32x4 acc_w[kWavesWide][kLanes];
-  __shared__ float max_w[kWavesWide], sum_w[kWavesWide];
-  __shared__ float z_new;
-  const const_i32_ptr row = as_constant(a.items) + size_t(blockIdx.x) * kItemInts;
-  const int seq = row[0];
-  const int kvh = row[1];
-  const int base = row[2];
-  const int n = row[3];
-  const int g = a.group;
-  const int h = int(blockIdx.y);
-  const int d4 = int(threadIdx.x) % kLanes;
-  const int slice = int(threadIdx.x) / kLanes;
-  const int wave = int(threadIdx.x) >> 6;
-  const int head = kvh * g + h;
-  const size_t orow = size_t(seq) * a.num_q_heads + head;
-
-  // Maximum (log2 units), weight sum and weighted sum of this slice's
-  // segments. A slice may have none, and a segment no token (appending): a
-  // maximum of -inf is replaced by 0 in the exponents, which gives weight 0.
-  float mx = -__builtin_inff(), wsum = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  auto add = [&](float l, float w0, const f32x4& o) {
-    const float mnew = fmaxf(mx, l);
-    const float mref = mnew == -__builtin_inff() ? 0.f : mnew;
-    const float keep = fast_exp2(mx - mref);
-    const float w = fast_exp2(l - mref);
-    acc = acc * keep + o * w;
-    wsum = wsum * keep + w0 * w;
-    mx = mnew;
-  };
-  {
-    const float* lse_h = a.part_lse + size_t(base) * g + h;
-    const float* o_h = a.part_o + (size_t(base) * g + h) * D + 4 * d4;
-#pragma unroll 4
-    for (int c = slice; c < n; c += kSlices)
-      add(lse_h[size_t(c) * g], 1.f, *reinterpret_cast<const f32x4*>(o_h + size_t(c) * g * D));
-  }
-  if constexpr (kAppend) {
-    if (wave == 0) {   // the newest token's score: lanes 0 .. D / 8 - 1, 8 dims each
-      float z = 0.f;
-      const int part = lane_id();
-      if (part < D / 8) {
-        const u32x4 qv = load16(a.q + orow * D + 8 * part);
-        const u32x4 kv = load16(a.k_new + (size_t(seq) * a.num_kv_heads + kvh) * D + 8 * part);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          z += bf16_value(qv[e] & 0xFFFFu) * bf16_value(kv[e] & 0xFFFFu);
-          z += bf16_value(qv[e] >> 16) * bf16_value(kv[e] >> 16);
-        }
-      }
-#pragma unroll
-      for (int off = 8; off >= 1; off >>= 1) z += __shfl_xor(z, off);
-      if (part == 0) z_new = z * a.scale_log2;
-    }
-  }
-  // the slices of a wave, then the waves
-#pragma unroll
-  for (int off = kLanes; off < 64; off <<= 1) {
-    f32x4 o;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(acc[i], off);
-    const float m2 = __shfl_xor(mx, off), w2 = __shfl_xor(wsum, off);
-    add(m2, w2, o);
-  }
-  if (lane_id() < kLanes) acc_w[wave][d4] = acc;
-  if (lane_id() == 0) {
-    max_w[wave] = mx;
-    sum_w[wave] = wsum;
-  }
-  __syncthreads();
-  if (int(threadIdx.x) < kLanes) {
-#pragma unroll
-    for (int w = 1; w < kWavesWide; ++w) add(max_w[w], sum_w[w], acc_w[w][d4]);
-    if constexpr (kAppend) {
-      const u32x2 vv = *reinterpret_cast<const u32x2*>(a.v_new + (size_t(seq) * a.num_kv_heads + kvh) * D + 4 * d4);
-      add(z_new, 1.f, f32x4{bf16_value(vv[0] & 0xFFFFu), bf16_value(vv[0] >> 16), bf16_value(vv[1] & 0xFFFFu),
-                            bf16_value(vv[1] >> 16)});
-    }
-    *reinterpret_cast<f32x4*>(a.out + orow * D + 4 * d4) = acc * (1.f / wsum);
-    if (a.lse && d4 == 0) a.lse[orow] = (mx + __log2f(wsum)) * kLn2;
-  }
-  if constexpr (kAppend) {
-    if (h == 0 && wave == 1) {   // store the token, once per pair
-      const int t = row[4] - 1;
-      const size_t entry = size_t(seq) * a.bt_stride + t / kPage;
-      const int fresh = a.new_pages ? as_constant(a.new_pages)[seq] : -1;
-      const int page = fresh >= 0 ? fresh : as_constant(a.block_table)[entry];
-      store_token<D>(a.k_dst, a.v_dst, a.k_new, a.v_new, a.num_kv_heads, seq, kvh, page, t % kPage, lane_id());
-      if (fresh >= 0 && kvh == 0 && lane_id() == 0) a.bt_dst[entry] = fresh;
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // test support: dense copy of one (sequence, KV head) through the same translation
 // ---------------------------------------------------------------------------
@@ -1311,24 +1322,22 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream, hipEvent_t st
 constexpr int kWideSegments = 4;
 
 template <int D>
-hipError_t launch_combine_d(CombineArgs a, hipStream_t stream) {
-  const bool append = a.k_new != nullptr;
-  if (a.num_items > 0 && a.num_partials >= int64_t(kWideSegments) * a.num_items) {
-    const dim3 grid(a.num_items, a.group), block(kWideThreads);
-    if (append)
-      hipLaunchKernelGGL((combine_wide_kernel<D, true>), grid, block, 0, stream, a);
+hipError_t launch_combine_d(const CombineArgs& a, hipStream_t stream) {
+  const bool wide = a.num_items > 0 && a.num_partials >= int64_t(kWideSegments) * a.num_items;
+  if (a.k_new) {
+    const int blocks = a.num_items * (wide ? a.group : 1) + (a.single_rows ? a.num_single : a.num_work);
+    if (blocks == 0) return hipSuccess;
+    if (wide)
+      hipLaunchKernelGGL((merge_append_kernel<D, true>), dim3(blocks), dim3(256), 0, stream, a);
     else
-      hipLaunchKernelGGL((combine_wide_kernel<D, false>), grid, block, 0, stream, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    a.num_items = 0;
+      hipLaunchKernelGGL((merge_append_kernel<D, false>), dim3(blocks), dim3(256), 0, stream, a);
+    return hipGetLastError();
   }
-  const int blocks = a.num_items + (!append ? 0 : a.single_rows ? a.num_single : a.num_work);
-  if (blocks == 0) return hipSuccess;
-  if (append)
-    hipLaunchKernelGGL(merge_append_kernel<D>, dim3(blocks), dim3(256), 0, stream, a);
+  if (a.num_items == 0) return hipSuccess;
+  if (wide)
+    hipLaunchKernelGGL(combine_wide_kernel<D>, dim3(a.num_items, a.group), dim3(kWideThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(combine_kernel, dim3(blocks), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(combine_kernel, dim3(a.num_items), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
