@@ -241,7 +241,7 @@ sf_status sf_decode_attn_append(const sf_attn_desc* desc, const sf_plan_info* in
  * Native per-step runner. A rollout instance runs one batched decode step
  * after another (App. B.1), so host work between steps is on the critical
  * path once the kernels are short. sf_runner_step does, in one call: plan
- * (sf_decode_attn_plan with the runner's options) into a pinned, device-
+ * (sf_runner_plan with the runner's options) into a pinned, device-
  * mapped host buffer, then on the caller's stream the attention (plain,
  * appending or fp8) and the merge of split sequences, whose kernels read that
  * work list in place (no separate upload). The runner owns a ring of 32 such
@@ -272,7 +272,7 @@ void sf_runner_destroy(sf_runner* runner);
 /* Sizes the runner's buffers ahead of its steps: the split-K workspace to at
  * least workspace_bytes, and every ring buffer to hold a work list of
  * work_bytes plus an appending step's extras for up to max_num_seqs
- * sequences; workspace_bytes and work_bytes as sf_decode_attn_plan reports
+ * sequences; workspace_bytes and work_bytes as sf_runner_plan reports
  * them (work_host NULL) for the largest batch the caller will step, with the
  * runner's options. Growing the workspace synchronizes `stream` first (the
  * old one may still be in use); a ring buffer grows after the step that last
@@ -282,6 +282,20 @@ void sf_runner_destroy(sf_runner* runner);
  * negative max_num_seqs, SF_ERR_HIP if an allocation fails. */
 sf_status sf_runner_reserve(sf_runner* runner, uint64_t workspace_bytes, uint64_t work_bytes,
                             int32_t max_num_seqs, void* stream);
+/* The plan of a runner's step (host only, arguments as sf_decode_attn_plan;
+ * kind: 0 a plain step, 1 over an fp8 cache, 2 appending). With options that leave the slices to the planner
+ * (chunk_pages, workers_per_cu, min_chunk_pages and xcd_parity_skew 0) and few
+ * pages per worker, each (sequence, KV head) pair is cut into equal segments
+ * where an estimate finds that faster than equal slices. A workgroup of G = 1,
+ * 2, 4 or 8 workers takes one segment, each worker an equal part of its pages
+ * (its table row), and merges the parts itself; workers_per_group is then
+ * SF_PLAN_SHARED_GROUPS + G, which only the runner accepts (sf_decode_attn
+ * returns SF_ERR_PLAN_MISMATCH; the step's *info reports G). Items are the
+ * segments, one per G table rows. Otherwise the plan is sf_decode_attn_plan's,
+ * with 8 workers per CU for an fp8 step that leaves them to the planner. */
+#define SF_PLAN_SHARED_GROUPS 16
+sf_status sf_runner_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts,
+                         int32_t kind, int32_t* work_host, uint64_t work_capacity_bytes, sf_plan_info* info);
 /* One decode step: desc (its head counts, head_dim and page size as at
  * creation), seq_lens_host (host int32 [num_seqs]) and the device tensors as
  * for sf_decode_attn; extras may be NULL. *info (may be NULL) receives the

@@ -126,6 +126,8 @@ def lib():
     L.sf_runner_extend.argtypes = [vp, P(sf_attn_desc), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, P(sf_runner_memory),
                                    vp, P(sf_extend_info)]
     L.sf_debug_extend_plan.argtypes = [P(sf_attn_desc), vp, vp, ctypes.c_int32, ctypes.c_int32, vp, ctypes.c_uint64, vp]
+    L.sf_runner_plan.argtypes = [P(sf_attn_desc), vp, P(sf_plan_opts), ctypes.c_int32, vp, ctypes.c_uint64,
+                                 P(sf_plan_info)]
     L.sf_page_pool_create.argtypes = [ctypes.c_int32, P(vp)]
     L.sf_page_pool_destroy.argtypes = [vp]
     L.sf_page_pool_destroy.restype = None
@@ -148,7 +150,7 @@ def lib():
                "sf_decode_attn_append", "sf_page_pool_create", "sf_page_pool_claim", "sf_page_pool_alloc",
                "sf_page_pool_release", "sf_page_table_step", "sf_route", "sf_extend_attn_plan",
                "sf_extend_attn", "sf_decode_attn_fp8", "sf_kv_quantize_fp8", "sf_runner_create",
-               "sf_runner_step", "sf_runner_extend", "sf_debug_extend_plan", "sf_debug_stream_read", "sf_decode_attn_scratch"):
+               "sf_runner_step", "sf_runner_extend", "sf_runner_plan", "sf_debug_extend_plan", "sf_debug_stream_read", "sf_decode_attn_scratch"):
         getattr(L, fn).restype = ctypes.c_int
     L.sf_status_string.argtypes = [ctypes.c_int]
     L.sf_status_string.restype = ctypes.c_char_p
@@ -743,12 +745,11 @@ class DecodeAttention:
         lens = np.ascontiguousarray(seq_lens, dtype=np.int32)
         desc = make_desc(lens.size, self.hq, self.hkv, self.d, block_table_stride, num_pages, 1.0)
         o = self.opts
-        wpc = o.workers_per_cu or (8 if fp8 else 0)
-        opts = sf_plan_opts(o.num_cus, int(chunk_pages or 0), wpc, o.min_chunk_pages, o.xcd_parity_skew)
+        opts = sf_plan_opts(o.num_cus, int(chunk_pages or 0), o.workers_per_cu, o.min_chunk_pages, o.xcd_parity_skew)
         info = sf_plan_info()
-        st = self.L.sf_decode_attn_plan(ctypes.byref(desc), lens.ctypes.data, ctypes.byref(opts), None, 0,
-                                        ctypes.byref(info))
-        _check("sf_decode_attn_plan", st)
+        st = self.L.sf_runner_plan(ctypes.byref(desc), lens.ctypes.data, ctypes.byref(opts), int(bool(fp8)), None, 0,
+                                   ctypes.byref(info))
+        _check("sf_runner_plan", st)
         main = stream or torch.cuda.current_stream(self.device)
         with torch.cuda.device(self.device):
             _check("sf_runner_reserve", self.L.sf_runner_reserve(self._runner(chunk_pages), info.workspace_bytes,

@@ -113,7 +113,7 @@ sf_status attend(const sf_attn_desc* desc, const sf_plan_info* info, const int32
                  const int32_t* block_table, float* out, float* lse, void* workspace,
                  uint64_t workspace_bytes, void* stream, const AppendArgs* app,
                  const float* k_scale = nullptr, const float* v_scale = nullptr, const RowCopy* copy = nullptr,
-                 void* attn_start = nullptr, void* attn_end = nullptr) {
+                 void* attn_start = nullptr, void* attn_end = nullptr, bool shared_groups = false) {
   sf_status st = check_step_args(desc, info, work_dev, q, k_pool, v_pool, block_table, out, lse,
                                  app ? app->k_new : nullptr, app ? app->v_new : nullptr,
                                  app ? app->new_pages : nullptr, k_scale, v_scale);
@@ -136,6 +136,7 @@ sf_status attend(const sf_attn_desc* desc, const sf_plan_info* info, const int32
   a.items = work_dev + table_rows(info->num_workers) * kItemInts;
   a.num_workers = info->num_workers;
   a.workers_per_group = info->workers_per_group;
+  a.shared_groups = shared_groups;
   a.q = static_cast<const uint16_t*>(q);
   a.k_pool = static_cast<const uint16_t*>(k_pool);
   a.v_pool = static_cast<const uint16_t*>(v_pool);
@@ -178,22 +179,22 @@ sf_status sf::decode_attn_append_rows(const sf_attn_desc* desc, const sf_plan_in
                                       const int32_t* new_pages, const int32_t* single_rows, int32_t num_single,
                                       void* k_pool, void* v_pool, int32_t* block_table, float* out, float* lse,
                                       void* workspace, uint64_t workspace_bytes, void* stream,
-                                      const RowCopy* copy, void* attn_start, void* attn_end) {
+                                      const RowCopy* copy, void* attn_start, void* attn_end, bool shared_groups) {
   if (num_single < 0 || (info && num_single > info->num_work) || (num_single > 0 && !single_rows) ||
       (single_rows && !aligned16(single_rows)))
     return SF_ERR_INVALID_ARG;
   const AppendArgs app = {q, k_new, v_new, new_pages, single_rows, num_single};
   return attend(desc, info, nullptr, work_dev, q, k_pool, v_pool, block_table, out, lse, workspace,
-                workspace_bytes, stream, &app, nullptr, nullptr, copy, attn_start, attn_end);
+                workspace_bytes, stream, &app, nullptr, nullptr, copy, attn_start, attn_end, shared_groups);
 }
 
 sf_status sf::decode_attn_rows(const sf_attn_desc* desc, const sf_plan_info* info, int32_t* work_dev, const void* q,
                                const void* k_pool, const void* v_pool, const float* k_scale, const float* v_scale,
                                const int32_t* block_table, float* out, float* lse, void* workspace,
                                uint64_t workspace_bytes, void* stream, const RowCopy* copy, void* attn_start,
-                               void* attn_end) {
+                               void* attn_end, bool shared_groups) {
   sf_status st = attend(desc, info, nullptr, work_dev, q, k_pool, v_pool, block_table, out, lse, workspace,
-                        workspace_bytes, stream, nullptr, k_scale, v_scale, copy, attn_start, attn_end);
+                        workspace_bytes, stream, nullptr, k_scale, v_scale, copy, attn_start, attn_end, shared_groups);
   if (st != SF_OK) return st;
   if (info->num_workers == 0 || info->num_combine == 0) return st;
   const bool copying = copy && copy->ints > 0 && copy->ints <= int64_t(64) * info->num_workers;

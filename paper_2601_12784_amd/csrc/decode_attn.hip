@@ -527,8 +527,9 @@ __device__ __forceinline__ void flush_stash(const AttnArgs& a, const Segment& sg
 // result: vector memory operations complete in issue order, so loads issued
 // after the stores would wait for the stores' completion too. stash (LDS, or
 // NULL): keep the result there instead of storing it (the worker stores it
-// last).
-template <int D, bool kAppend>
+// last). kShared: the stashed lse is in log2 units whatever the slot (the
+// workgroup merges its waves' results).
+template <int D, bool kAppend, bool kShared = false>
 __device__ __forceinline__ void attend_segment(const AttnArgs& a, const Segment& item, WorkerRows& w, int index,
                                                SegmentRegs<D>& r, bool& primed, float* stash) {
   constexpr int JB = Shape<D>::JB;
@@ -590,7 +591,8 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, const Segment&
   f32x4 o[JB];
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb) o[jb] = st.o[jb] * inv;
-  const float l = slot < 0 ? (lt > 0.f ? (st.m + __log2f(lt)) * kLn2 : -__builtin_inff()) : st.m + __log2f(lt);
+  const float l = slot < 0 && !kShared ? (lt > 0.f ? (st.m + __log2f(lt)) * kLn2 : -__builtin_inff())
+                                       : st.m + __log2f(lt);
   if (stash) {
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
@@ -602,12 +604,67 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, const Segment&
   write_result<D>(a, item, o, l);
 }
 
+// Merges the stashed results of a workgroup whose kWG waves took one segment
+// together (a plan of shared groups), and stores it: wave w takes the output
+// blocks w, w + kWG .. of 16 dims. A wave without a token has lse -inf and
+// weight 0.
+template <int D, int kWG>
+__device__ __forceinline__ void merge_group(const AttnArgs& a, const Segment& sg, const float (*stash)[(4 * Shape<D>::JB + 1) * 64]) {
+  constexpr int JB = Shape<D>::JB;
+  const int lane = lane_id();
+  const int col = lane & 15;
+  const int grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  __syncthreads();
+  float l[kWG];
+  float mx = -__builtin_inff();
+#pragma unroll
+  for (int i = 0; i < kWG; ++i) {
+    l[i] = stash[i][4 * JB * 64 + lane];
+    mx = fmaxf(mx, l[i]);
+  }
+  const float mref = mx == -__builtin_inff() ? 0.f : mx;
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < kWG; ++i) {
+    l[i] = fast_exp2(l[i] - mref);
+    sum += l[i];
+  }
+  const float inv = sum == 0.f ? 0.f : 1.f / sum;
+  const int g = a.group;
+  if (col >= g) return;
+  const int head = sg.kvh * g + col;
+  const bool part = sg.slot >= 0;
+  float* dst = (part ? a.part_o + (size_t(sg.slot) * g + col) * D : a.out + (size_t(sg.seq) * a.num_q_heads + head) * D) + 4 * grp;
+#pragma unroll
+  for (int j = 0; j < (JB + kWG - 1) / kWG; ++j) {
+    const int jb = wave + j * kWG;
+    if (jb >= JB) break;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < kWG; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] += l[i] * stash[i][(4 * jb + e) * 64 + lane];
+    *reinterpret_cast<f32x4*>(dst + 16 * jb) = o * inv;
+  }
+  if (wave == 0 && grp == 0) {
+    const float lse = mx + __log2f(sum);   // -inf without a token
+    if (part)
+      a.part_lse[size_t(sg.slot) * g + col] = lse;
+    else if (a.lse)
+      a.lse[size_t(sg.seq) * a.num_q_heads + head] = lse * kLn2;
+  }
+}
+
 // One wave per worker: its segments are consecutive in the work list and
 // together cover the same number of KV pages as every other worker's.
 // Two waves per SIMD (at most 256 registers) keep 2048 workers resident.
 // The appending variant reads the newest tokens from k_new / v_new and
 // stores nothing: the stores come in the merge launch that follows.
-template <int D, bool kAppend, int kWG>
+// kShared: the workgroup's waves take one segment together (a part of it
+// each, one item per worker) and merge their results in LDS, so a short pair
+// needs neither partial results nor a merge launch for its parallelism.
+template <int D, bool kAppend, int kWG, bool kShared>
 __global__ __launch_bounds__(64 * kWG) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_worker_kernel(AttnArgs a) {
   // A worker's first segment is usually the tail of a pair cut by the
   // previous worker, and short: its result would be written early, into the
@@ -620,6 +677,12 @@ __global__ __launch_bounds__(64 * kWG) __attribute__((amdgpu_waves_per_eu(2, 2))
   float* stash = stash_all[w.worker - int(blockIdx.x) * kWG];
   SegmentRegs<D> regs;
   bool primed = false;
+  if constexpr (kShared) {
+    attend_segment<D, kAppend, true>(a, w.head, w, 0, regs, primed, stash);
+    merge_group<D, kWG>(a, w.head, stash_all);
+    row_copy_store(a, w);
+    return;
+  }
   Segment sg = w.head;
   for (int i = 0; i < w.count; ++i) {
     attend_segment<D, kAppend>(a, sg, w, i, regs, primed, i == 0 && w.count > 1 ? stash : nullptr);
@@ -742,7 +805,7 @@ __device__ __forceinline__ void widen_v(const VHalf8<D>& r, VHalf<D>& b) {
 }
 
 // One segment over an fp8 cache; otherwise as attend_segment.
-template <int D, int R>
+template <int D, int R, bool kShared = false>
 __device__ __forceinline__ void attend_segment_fp8(const AttnArgs& a, const Segment& item, WorkerRows& w, int index,
                                                    float* stash) {
   constexpr int KB = Shape<D>::KB;
@@ -832,7 +895,8 @@ __device__ __forceinline__ void attend_segment_fp8(const AttnArgs& a, const Segm
   f32x4 o[JB];
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb) o[jb] = st.o[jb] * inv;
-  const float l = slot < 0 ? (lt > 0.f ? (st.m + __log2f(lt)) * kLn2 : -__builtin_inff()) : st.m + __log2f(lt);
+  const float l = slot < 0 && !kShared ? (lt > 0.f ? (st.m + __log2f(lt)) * kLn2 : -__builtin_inff())
+                                       : st.m + __log2f(lt);
   if (stash) {
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
@@ -844,7 +908,7 @@ __device__ __forceinline__ void attend_segment_fp8(const AttnArgs& a, const Segm
   write_result<D>(a, item, o, l);
 }
 
-template <int D, int kWG>
+template <int D, int kWG, bool kShared>
 __global__ __launch_bounds__(64 * kWG) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_worker_fp8_kernel(AttnArgs a) {
   // The worker's first result waits in LDS, as in attn_worker_kernel.
   __shared__ float stash_all[kWG][(4 * Shape<D>::JB + 1) * 64];
@@ -852,6 +916,12 @@ __global__ __launch_bounds__(64 * kWG) __attribute__((amdgpu_waves_per_eu(2, 2))
   WorkerRows w;
   if (!worker_rows<kWG>(a, rows_lds, w)) return;
   float* stash = stash_all[w.worker - int(blockIdx.x) * kWG];
+  if constexpr (kShared) {
+    attend_segment_fp8<D, 3, true>(a, w.head, w, 0, stash);
+    merge_group<D, kWG>(a, w.head, stash_all);
+    row_copy_store(a, w);
+    return;
+  }
   Segment sg = w.head;
   for (int i = 0; i < w.count; ++i) {
     attend_segment_fp8<D, 3>(a, sg, w, i, i == 0 && w.count > 1 ? stash : nullptr);
@@ -1290,21 +1360,29 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
 // of their table rows; other plans keep one worker per workgroup, spread
 // over every CU. Workgroup b holds workers G b .. G b + G - 1 and runs on
 // XCD b mod 8.
-template <int kWG>
+template <int kWG, bool kShared>
 void (*pick_attention(const AttnArgs& a))(AttnArgs) {
-  if (a.k_scale) return a.head_dim == 128 ? attn_worker_fp8_kernel<128, kWG> : attn_worker_fp8_kernel<64, kWG>;
-  if (a.k_new) return a.head_dim == 128 ? attn_worker_kernel<128, true, kWG> : attn_worker_kernel<64, true, kWG>;
-  return a.head_dim == 128 ? attn_worker_kernel<128, false, kWG> : attn_worker_kernel<64, false, kWG>;
+  const bool d128 = a.head_dim == 128;
+  if (a.k_scale) return d128 ? attn_worker_fp8_kernel<128, kWG, kShared> : attn_worker_fp8_kernel<64, kWG, kShared>;
+  if (a.k_new)
+    return d128 ? attn_worker_kernel<128, true, kWG, kShared> : attn_worker_kernel<64, true, kWG, kShared>;
+  return d128 ? attn_worker_kernel<128, false, kWG, kShared> : attn_worker_kernel<64, false, kWG, kShared>;
 }
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
   if (a.num_workers == 0) return hipSuccess;
   const int per_group = a.workers_per_group;   // 1, 2, 4 or 8 (checked with the plan)
   const dim3 grid((a.num_workers + per_group - 1) / per_group), block(64 * per_group);
-  void (*kernel)(AttnArgs) = per_group == 8   ? pick_attention<8>(a)
-                             : per_group == 4 ? pick_attention<4>(a)
-                             : per_group == 2 ? pick_attention<2>(a)
-                                              : pick_attention<1>(a);
+  void (*kernel)(AttnArgs) = nullptr;
+  if (a.shared_groups && per_group > 1)
+    kernel = per_group == 8   ? pick_attention<8, true>(a)
+             : per_group == 4 ? pick_attention<4, true>(a)
+                              : pick_attention<2, true>(a);
+  else
+    kernel = per_group == 8   ? pick_attention<8, false>(a)
+             : per_group == 4 ? pick_attention<4, false>(a)
+             : per_group == 2 ? pick_attention<2, false>(a)
+                              : pick_attention<1, false>(a);
   if (start || stop)
     hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, a);
   else

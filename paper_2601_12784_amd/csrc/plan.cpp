@@ -372,3 +372,215 @@ extern "C" sf_status sf_decode_attn_plan(const sf_attn_desc* desc, const int32_t
   }
   return row == n_work ? SF_OK : SF_ERR_INVALID_ARG;
 }
+
+// ---------------------------------------------------------------------------
+// the runner's plan
+// ---------------------------------------------------------------------------
+namespace {
+
+// Batches of few pages per worker are latency bound: the attention kernel
+// takes as long as its slowest worker, and each segment after a worker's first
+// costs about 3 us of dependent loads (query, block table, first block), more
+// than the equal slices save. For them the runner cuts the pairs themselves
+// into equal segments of at most `most` pages, one per workgroup of 1 to 8
+// waves that share its pages and merge in LDS; where no pair is cut there is
+// no merge launch. Attention + merge kernels (us) with equal slices and with
+// whole segments (28/4 heads, head_dim 128, unless noted; W waves in groups
+// of G):
+//   4 sequences of 17 .. 300 tokens, 4/1 heads, D = 64   12.2   6.2 (W 16, G 4)
+//   1 of 1000 tokens                                     10.5  10.5 (W 256, G 4, cut)
+//   1 of 32768                                           22.9  20.5 (W 1024, G 4, cut)
+//   16 of 1000                                           19.8  16.5 (W 1024, G 4, cut)
+//   64 of up to 600                                      20.9  15.8 (W 2048, G 8)
+//   300 of up to 80                                      29.0  15.5 (W 1200, G 1)
+//   40 of up to 300, 40/8 heads                          26.5  13.4 (W 1280, G 4)
+//   200 of up to 200 and two of 16000 and 9000           41.6  35.2 (W 1020, G 1, cut)
+//   the last four over an fp8 cache: 19.7  16.8, 27.1  12.9, 24.3  11.3, 39.8  24.3
+// With many pages per worker the slices' balance wins: 64 sequences of 512 to
+// 4096 tokens 57.1 and 56.9 us, 128 of them 99.3 and 104.4. Groups of 8 where
+// workgroups are few load few CUs: 16 sequences of 1000 tokens 17.9 us with G
+// 8 and no cut, against 12.2 + 4.3.
+//
+// Both plans' times are estimated (us, fitted to those measurements): the
+// attention kernel is the longer of its slowest worker (launch, waves to start,
+// pages one after another, segments after its first) and the stream of the
+// whole batch's bytes; cut pairs add the merge launch (depth: segments of the
+// pair cut most).
+struct RunnerCost {
+  double page;       // a page in one of many waves; half that in a lone one
+  double gbytes;     // GB/s of the whole chip
+  double bytes;      // K and V bytes of a page
+  double merge;      // the merge launch, or what cut pairs add to an appending step's
+  int64_t cus;
+};
+constexpr double kLaunchUs = 4.0, kWaveUs = 0.002, kSegmentUs = 3.0, kStreamUs = 6.5;
+constexpr double kShareUs = 0.3, kMergeUs = 4.0, kMergeAppendUs = 0.5, kPartialUs = 0.0005, kDepthUs = 0.014;
+constexpr int64_t kDepth = 128;   // segments of a pair that the merge takes without more time
+// Pages per worker (at 4 per CU) beyond which the slices are always taken.
+constexpr int64_t kRunnerPages = 40;
+
+double runner_estimate(const RunnerCost& c, int64_t total, int64_t workers, int64_t longest, int64_t extra_segments,
+                       int64_t partials, int64_t depth, int32_t sharing = 1) {
+  const double page = c.page * (0.5 + 0.5 * std::min(1.0, double(workers) / double(2 * c.cus))) * (1.0 + 0.065 * (sharing - 1));
+  const double worker = kLaunchUs + kWaveUs * double(workers) + page * double(longest) + kSegmentUs * double(extra_segments) +
+                        kShareUs * (sharing - 1);
+  // workers of unequal length do not draw the full rate to the end
+  const double uneven = std::max(1.0, double(longest) * double(workers) / double(total));
+  const double stream = kStreamUs + double(total) * c.bytes / (c.gbytes * 1e3) * (0.5 + 0.5 * uneven);
+  return std::max(worker, stream) +
+         (partials > 0 ? c.merge + kPartialUs * double(partials) + kDepthUs * double(std::max<int64_t>(0, depth - kDepth)) : 0.0);
+}
+
+}  // namespace
+
+sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts,
+                                 StepKind kind, int32_t* work_host, uint64_t work_capacity_bytes, sf_plan_info* info) {
+  const bool fp8 = kind == StepKind::kFp8, append = kind == StepKind::kAppend;
+  sf_plan_opts o = {};
+  if (opts) o = *opts;
+  // The caller's own choice of slices stands.
+  const bool free_choice =
+      o.chunk_pages == 0 && o.workers_per_cu == 0 && o.min_chunk_pages == 0 && o.xcd_parity_skew == 0 && o.num_cus >= 0;
+  if (fp8 && o.workers_per_cu == 0) o.workers_per_cu = kFp8WorkersPerCu;
+  auto slices = [&]() {
+    return sf_decode_attn_plan(desc, seq_lens_host, &o, work_host, work_capacity_bytes, info);
+  };
+  if (!free_choice || validate_desc(desc) != SF_OK || !info || desc->num_seqs == 0 || !seq_lens_host) return slices();
+
+  const int64_t cus = o.num_cus ? o.num_cus : kDefaultNumCus;
+  const int64_t hkv = desc->num_kv_heads, g = desc->num_q_heads / hkv;
+  const int32_t B = desc->num_seqs;
+  int64_t total = 0, empty = 0;
+  for (int32_t s = 0; s < B; ++s) {
+    const int32_t L = seq_lens_host[s];
+    if (L < 0 || (L > 0 && desc->num_pages == 0)) return SF_ERR_INVALID_ARG;
+    const int64_t npg = (int64_t(L) + kPage - 1) / kPage;
+    if (npg > desc->block_table_stride) return SF_ERR_INVALID_ARG;
+    total += npg * hkv;
+    empty += npg == 0 ? hkv : 0;
+  }
+  const int64_t pairs = int64_t(B) * hkv - empty;
+  if (total == 0 || total > kRunnerPages * 4 * cus || pairs + empty > 8 * cus) return slices();
+
+  // Segments of at most `most` pages: their number (an empty pair is one), the
+  // cut pairs and their segments.
+  struct Count {
+    int64_t segments = 0, cut = 0, partials = 0, longest = 0;
+  };
+  auto count = [&](int32_t most) {
+    Count c;
+    for (int32_t s = 0; s < B; ++s) {
+      const int32_t n = (seq_lens_host[s] + kPage - 1) / kPage;
+      const int32_t k = n <= most ? 1 : (n + most - 1) / most;
+      c.segments += k;
+      if (k > 1) ++c.cut, c.partials += k;
+      c.longest = std::max<int64_t>(c.longest, (n + k - 1) / k);
+    }
+    c.segments *= hkv;
+    c.cut *= hkv;
+    c.partials *= hkv;
+    return c;
+  };
+  const RunnerCost cost = {(fp8 ? 0.75 : 0.95) * (desc->head_dim == 64 ? 0.75 : 1.0),
+                           (fp8 ? 5700.0 : 6000.0) * double(cus) / 256, double(kPage) * desc->head_dim * (fp8 ? 2 : 4),
+                           append ? kMergeAppendUs : kMergeUs, cus};
+  // The slices: segments of the worker that has most, i.e. pairs that a window
+  // of one slice can touch, walked over the sequences (hkv equal pairs each).
+  const int64_t wpc = o.workers_per_cu ? o.workers_per_cu : kDefaultWorkersPerCu;
+  const int64_t slice_workers = std::min<int64_t>(wpc * cus, (total + kDefaultMinChunk - 1) / kDefaultMinChunk);
+  const int64_t slice = (total + slice_workers - 1) / slice_workers;
+  int64_t most_segments = 1, window = 0, window_pairs = 0, longest_pair = 0;
+  bool whole_pairs = total % slice_workers == 0;   // every slice is one pair
+  for (int32_t s = 0, first = 0; s < B; ++s) {
+    const int64_t n = (seq_lens_host[s] + kPage - 1) / kPage;
+    if (n == 0) continue;
+    whole_pairs = whole_pairs && n == slice;
+    longest_pair = std::max(longest_pair, n);
+    window += n * hkv;
+    window_pairs += hkv;
+    while (window > slice && first < s) {
+      const int64_t m = (seq_lens_host[first] + kPage - 1) / kPage;
+      if (m > 0) window -= m * hkv, window_pairs -= hkv;
+      ++first;
+    }
+    most_segments = std::max(most_segments, window <= slice ? window_pairs + 1 : std::min(hkv, slice / n) + 1);
+  }
+  double best_us = runner_estimate(cost, total, slice_workers, slice, whole_pairs ? 0 : most_segments - 1,
+                                   whole_pairs ? 0 : slice_workers + std::min(pairs, slice_workers), longest_pair / slice + 1);
+  int32_t best = 0, waves = 1;
+  Count chosen;
+  for (const int32_t g8 : {1, 2, 4, 8}) {
+    if ((pairs + empty) * g8 > 8 * cus) break;
+    int64_t last = 0;
+    auto consider = [&](int64_t most) {
+      if (most == last) return;
+      last = most;
+      const Count c = count(int32_t(most));
+      const double us = runner_estimate(cost, total, c.segments * g8, (c.longest + g8 - 1) / g8, 0, c.partials,
+                                        (longest_pair + most - 1) / most, g8);
+      if (us < best_us) best_us = us, best = int32_t(most), waves = g8, chosen = c;
+    };
+    consider(longest_pair);   // every pair whole
+    for (const int64_t target : {2 * cus, 4 * cus, 8 * cus}) {
+      // the shortest segments that take at most `target` waves; more than four
+      // waves per CU only where the pairs alone need them
+      if ((pairs + empty) * g8 > target || (target > 4 * cus && (pairs + empty) * g8 <= 4 * cus)) continue;
+      int64_t most = std::max<int64_t>(g8, (total * g8 + target - 1) / target);
+      while (count(int32_t(most)).segments * g8 > target) most += std::max<int64_t>(1, most / 32);
+      consider(std::min(most, longest_pair));
+    }
+  }
+  if (best == 0) return slices();
+
+  const int64_t work = chosen.segments, workers = work * waves;
+  int32_t group = waves;
+  if (waves == 1)   // one segment per worker: the fewest waves per workgroup that give one round of workgroups
+    for (group = 1; group < 8 && workers > group * cus;) group *= 2;
+  info->num_workers = int32_t(workers);
+  info->num_work = int32_t(work);
+  info->num_combine = int32_t(chosen.cut);
+  info->num_partials = int32_t(chosen.partials);
+  info->chunk_pages = int32_t((chosen.longest + waves - 1) / waves);
+  info->workers_per_group = waves > 1 ? kSharedGroups + group : group;
+  info->work_bytes = uint64_t(workers + work + chosen.cut) * kItemInts * 4;
+  info->workspace_bytes = chosen.partials ? align256(uint64_t(chosen.partials) * g * desc->head_dim * 4) +
+                                                align256(uint64_t(chosen.partials) * g * 4)
+                                          : 0;
+  info->desc_key = desc_key(desc);
+  if (!work_host) return SF_OK;
+  if (work_capacity_bytes < info->work_bytes) return SF_ERR_CAPACITY;
+
+  int32_t* table = work_host;
+  int32_t* items = table + workers * kItemInts;
+  int32_t* comb = items + work * kItemInts;
+  int32_t item = 0, slot = 0, cut = 0;
+  for (int32_t s = 0; s < B; ++s) {
+    const int32_t L = seq_lens_host[s], n = (L + kPage - 1) / kPage;
+    const int32_t k = n <= best ? 1 : (n + best - 1) / best;
+    for (int32_t h = 0; h < hkv; ++h) {
+      if (k > 1) {
+        const int32_t c8[kItemInts] = {s, h, slot, k, L, 0, 0, 0};
+        std::memcpy(comb + int64_t(cut) * kItemInts, c8, sizeof c8);
+      }
+      for (int32_t i = 0; i < k; ++i, ++item) {
+        const int32_t b = int32_t(int64_t(i) * n / k), e = int32_t(int64_t(i + 1) * n / k);
+        const int32_t r8[kItemInts] = {s, h, b, e, L, k > 1 ? slot++ : -1, k > 1 ? cut : -1, k};
+        std::memcpy(items + int64_t(item) * kItemInts, r8, sizeof r8);
+        for (int32_t j = 0; j < waves; ++j) {
+          const int32_t pb = b + int32_t(int64_t(j) * (e - b) / waves), pe = b + int32_t(int64_t(j + 1) * (e - b) / waves);
+          const int32_t t8[kItemInts] = {item, 1, s, h, pb, pe, L, r8[5]};
+          std::memcpy(table + (int64_t(item) * waves + j) * kItemInts, t8, sizeof t8);
+        }
+      }
+      cut += k > 1;
+    }
+  }
+  return SF_OK;
+}
+
+extern "C" sf_status sf_runner_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts,
+                                    int32_t kind, int32_t* work_host, uint64_t work_capacity_bytes,
+                                    sf_plan_info* info) {
+  if (kind < 0 || kind > 2) return SF_ERR_INVALID_ARG;
+  return decode_plan_runner(desc, seq_lens_host, opts, StepKind(kind), work_host, work_capacity_bytes, info);
+}

@@ -20,6 +20,7 @@
 // how much more depended on whether the two streams shared a hardware queue.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <new>
 
@@ -33,7 +34,6 @@ namespace {
 constexpr int kRing = 32;
 constexpr int kMarkEvery = 16;
 constexpr int kMarks = 4;
-constexpr int kFp8WorkersPerCu = 8;
 // Without a store launch to copy the rows, a copy launch (about 4 us) pays from
 // about two rounds of workgroups on, each starting with a read over PCIe.
 constexpr int kExtendCopyParts = 512;
@@ -263,16 +263,17 @@ extern "C" sf_status sf_runner_step(sf_runner* r, const sf_attn_desc* desc, cons
   // An fp8 block moves half the bytes of a bf16 one: unless the caller chose,
   // fp8 steps plan two waves per SIMD (measured: kernel 129 us instead of 136
   // on the long-tail batch; bf16 is slower at 8).
-  sf_plan_opts opts = r->opts;
-  if (fp8 && opts.workers_per_cu == 0) opts.workers_per_cu = kFp8WorkersPerCu;
   sf_plan_info info;
-  st = sf_decode_attn_plan(desc, seq_lens_host, &opts, pin.ptr, pin.bytes, &info);
+  const sf::StepKind kind = fp8 ? sf::StepKind::kFp8 : append ? sf::StepKind::kAppend : sf::StepKind::kPlain;
+  st = sf::decode_plan_runner(desc, seq_lens_host, &r->opts, kind, pin.ptr, pin.bytes, &info);
   auto need = [&]() { return info.work_bytes + (append ? uint64_t(info.num_work) * 32 + pages_bytes : 0); };
   if (st == SF_ERR_CAPACITY || (st == SF_OK && pin.bytes < need())) {
     if ((st = grow_pinned(pin, need())) != SF_OK) return st;
-    st = sf_decode_attn_plan(desc, seq_lens_host, &opts, pin.ptr, pin.bytes, &info);
+    st = sf::decode_plan_runner(desc, seq_lens_host, &r->opts, kind, pin.ptr, pin.bytes, &info);
   }
   if (st != SF_OK) return st;
+  const bool shared = info.workers_per_group > sf::kSharedGroups;
+  if (shared) info.workers_per_group -= sf::kSharedGroups;
   int32_t num_single = 0;
   uint64_t pages_off = info.work_bytes;
   if (append && desc->num_seqs > 0) {
@@ -320,11 +321,11 @@ extern "C" sf_status sf_runner_step(sf_runner* r, const sf_attn_desc* desc, cons
                                      reinterpret_cast<const int32_t*>(wbase + info.work_bytes), num_single,
                                      const_cast<void*>(k_pool), const_cast<void*>(v_pool),
                                      const_cast<int32_t*>(block_table), out, lse, r->workspace,
-                                     r->workspace_bytes, stream, cp, ev0, ev1);
+                                     r->workspace_bytes, stream, cp, ev0, ev1, shared);
   } else {
     st = sf::decode_attn_rows(desc, &info, work, q, k_pool, v_pool, fp8 ? extras->k_scale : nullptr,
                               fp8 ? extras->v_scale : nullptr, block_table, out, lse, r->workspace,
-                              r->workspace_bytes, stream, cp, ev0, ev1);
+                              r->workspace_bytes, stream, cp, ev0, ev1, shared);
   }
   pin.used = true;
   pin.last_step = r->steps;
@@ -435,6 +436,11 @@ extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, u
                                        int32_t max_num_seqs, void* stream) {
   if (!r || max_num_seqs < 0) return SF_ERR_INVALID_ARG;
   hipStream_t main = static_cast<hipStream_t>(stream);
+  // Smaller batches than the one reserved for may be planned as whole segments
+  // of pairs, one per worker, up to four workers per CU of them partial.
+  const int64_t cus = r->opts.num_cus > 0 ? r->opts.num_cus : sf::kDefaultNumCus;
+  const uint64_t head_rows = uint64_t(4 * cus) * (r->shape.num_q_heads / r->shape.num_kv_heads);
+  workspace_bytes = std::max(workspace_bytes, sf::align256(head_rows * r->shape.head_dim * 4) + sf::align256(head_rows * 4));
   // partials, then the device copy of the merge rows (at most the work
   // list's size) and new_pages
   sf_status st = grow_device(r, &r->workspace, &r->workspace_bytes,

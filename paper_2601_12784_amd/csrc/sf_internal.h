@@ -22,7 +22,18 @@ constexpr int kDefaultMinChunk = 8;      // pages: fewer workers rather than thi
 // workers (sf_plan_opts.xcd_parity_skew; none by default).
 constexpr int kMaxParitySkew = 250;
 
+constexpr int kFp8WorkersPerCu = 8;      // the runner's fp8 steps (two waves per SIMD)
+
 sf_status validate_desc(const sf_attn_desc* d);
+
+// The plan of a runner's step (sf_runner_plan): sf_decode_attn_plan's equal
+// slices, or, for batches of few pages per worker, segments of pairs that a
+// workgroup's waves share. The latter report kSharedGroups + waves as
+// workers_per_group: only the runner launches them.
+constexpr int32_t kSharedGroups = SF_PLAN_SHARED_GROUPS;
+enum class StepKind { kPlain = 0, kFp8 = 1, kAppend = 2 };
+sf_status decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts, StepKind kind,
+                             int32_t* work_host, uint64_t work_capacity_bytes, sf_plan_info* info);
 inline int64_t table_rows(int64_t workers) { return workers; }   // worker-table rows of a plan
 uint64_t desc_key(const sf_attn_desc* d);
 uint64_t align256(uint64_t x);
@@ -38,7 +49,8 @@ struct AttnArgs {
   const int32_t* worker_table;  // (first item, item count) per worker
   const int32_t* items;         // segment rows
   int32_t num_workers;
-  int32_t workers_per_group;    // waves per workgroup (1, 4 or 8; the plan's choice)
+  int32_t workers_per_group;    // waves per workgroup (1, 2, 4 or 8; the plan's choice)
+  bool shared_groups;           // a workgroup's waves share one segment and merge in LDS
   const uint16_t* q;
   const uint16_t* k_pool;
   const uint16_t* v_pool;
@@ -224,7 +236,7 @@ sf_status decode_attn_append_rows(const sf_attn_desc* desc, const sf_plan_info* 
                                   const int32_t* single_rows, int32_t num_single, void* k_pool, void* v_pool,
                                   int32_t* block_table, float* out, float* lse, void* workspace,
                                   uint64_t workspace_bytes, void* stream, const RowCopy* copy,
-                                  void* attn_start = nullptr, void* attn_end = nullptr);
+                                  void* attn_start = nullptr, void* attn_end = nullptr, bool shared_groups = false);
 
 // sf_decode_attn (k_scale NULL) or sf_decode_attn_fp8, then the combine of
 // split pairs, on a device-resident or mapped work list; with `copy`, the
@@ -236,7 +248,7 @@ sf_status decode_attn_rows(const sf_attn_desc* desc, const sf_plan_info* info, i
                            const void* k_pool, const void* v_pool, const float* k_scale, const float* v_scale,
                            const int32_t* block_table, float* out, float* lse, void* workspace,
                            uint64_t workspace_bytes, void* stream, const RowCopy* copy, void* attn_start,
-                           void* attn_end);
+                           void* attn_end, bool shared_groups = false);
 hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream);
 
 // Every host-side check of a decode step's arguments except the workspace
