@@ -150,18 +150,44 @@ Split choose_split(const sf_attn_desc* desc, const int32_t* lens, const int32_t*
   const int32_t g = desc->num_q_heads / desc->num_kv_heads;
   const int64_t hkv = desc->num_kv_heads;
   const double step_scale = desc->head_dim / 128.0;
-  auto totals = [&](int32_t rows, int32_t most) {
+  // The blocks by length: (steps, blocks, rows), made once per item size; the
+  // search below asks for the totals of many cuts.
+  struct Walk {
+    int32_t steps, blocks;
+    int64_t rows;
+  };
+  thread_local std::vector<Walk> walks;
+  auto measure = [&](int32_t rows) {
+    walks.clear();
+    for_blocks(desc, lens, new_lens, rows / g, [&](int32_t, int32_t, int32_t nt, int32_t steps) {
+      if (walks.empty() || walks.back().steps != steps) walks.push_back({steps, 0, 0});
+      ++walks.back().blocks;
+      walks.back().rows += int64_t(nt) * g;
+    });
+    std::sort(walks.begin(), walks.end(), [](const Walk& x, const Walk& y) { return x.steps < y.steps; });
+    size_t n = 0;
+    for (const Walk& w : walks) {
+      if (n > 0 && walks[n - 1].steps == w.steps) {
+        walks[n - 1].blocks += w.blocks;
+        walks[n - 1].rows += w.rows;
+      } else {
+        walks[n++] = w;
+      }
+    }
+    walks.resize(n);
+  };
+  auto totals = [&](int32_t most) {
     Totals t;
     const float inv = 1.f / float(most);   // an estimate: the plan itself counts exactly
-    for_blocks(desc, lens, new_lens, rows / g, [&](int32_t, int32_t, int32_t nt, int32_t steps) {
-      const int32_t k = steps <= most ? 1 : int32_t(float(steps - 1) * inv) + 1;
-      const int32_t len = k == 1 ? steps : int32_t(float(steps) / float(k));
-      t.parts += k;
-      t.steps += steps;
-      if (k > 1) t.cut_rows += int64_t(k) * nt * g;
-      t.longest = std::max(t.longest, k == 1 ? steps : len + 1);
+    for (const Walk& w : walks) {
+      const int32_t k = w.steps <= most ? 1 : int32_t(float(w.steps - 1) * inv) + 1;
+      const int32_t len = k == 1 ? w.steps : int32_t(float(w.steps) / float(k));
+      t.parts += int64_t(k) * w.blocks;
+      t.steps += int64_t(w.steps) * w.blocks;
+      if (k > 1) t.cut_rows += k * w.rows;
+      t.longest = std::max(t.longest, k == 1 ? w.steps : len + 1);
       t.shortest = std::min(t.shortest, len);
-    });
+    }
     t.parts *= hkv;
     t.steps *= hkv;
     t.cut_rows *= hkv;
@@ -186,32 +212,48 @@ Split choose_split(const sf_attn_desc* desc, const int32_t* lens, const int32_t*
   };
 
   Split best = {kExtendRows, INT32_MAX};
-  const Totals whole = totals(kExtendRows, INT32_MAX);
-  if (whole.parts == 0 || whole.parts > int64_t(kRounds) * 2 * num_cus) return best;
+  int64_t items = 0;
+  for (int32_t s = 0; s < desc->num_seqs; ++s) items += (new_lens[s] + kExtendRows / g - 1) / (kExtendRows / g) * hkv;
+  if (items == 0 || items > int64_t(kRounds) * 2 * num_cus) return best;
+  measure(kExtendRows);
+  const Totals whole = totals(INT32_MAX);
   double best_us = estimate(whole, false);
   auto consider = [&](int32_t rows, const Totals& uncut) {
     const bool small = rows == kExtendSmallRows;
+    const int64_t slots = small ? 2 * num_cus : num_cus;
     auto take = [&](const Totals& t, int32_t most) {
       const double us = estimate(t, small);
       if (us < best_us) best_us = us, best = {rows, most};
     };
     take(uncut, INT32_MAX);
-    const int64_t slots = small ? 2 * num_cus : num_cus;
+    // no cut beats the average load
+    const Cost least = small ? kSmallAlone : kLarge;
+    if ((double(uncut.parts) * least.start + least.step * step_scale * double(uncut.steps)) / double(slots) >= best_us) return;
     for (int32_t r = 1; r <= kRounds; ++r) {
       // the shortest parts that number at most r per slot, and somewhat longer ones
       if (uncut.parts >= r * slots) continue;
-      double most = std::max<double>(kSmallestPart, double(uncut.steps) / double(r * slots));
-      Totals t;
-      for (; most < uncut.longest; most = std::max(most + 1.0, most * 1.03))
-        if ((t = totals(rows, int32_t(most))).parts <= r * slots) break;
-      if (most >= uncut.longest) continue;
-      take(t, int32_t(most));
-      for (const double longer : {1.25, 1.6})
-        if (longer * most < uncut.longest) take(totals(rows, int32_t(longer * most)), int32_t(longer * most));
+      int32_t lo = int32_t(std::max<int64_t>(kSmallestPart, uncut.steps / (r * slots))), hi = uncut.longest - 1;
+      if (lo > hi) break;   // parts of the least length already fill fewer rounds
+      Totals t = totals(hi);
+      if (t.parts > r * slots) continue;
+      while (lo < hi) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        const Totals m = totals(mid);
+        if (m.parts <= r * slots)
+          hi = mid, t = m;
+        else
+          lo = mid + 1;
+      }
+      take(t, hi);
+      for (const int32_t longer : {hi + hi / 4, hi + hi / 2})
+        if (longer < uncut.longest) take(totals(longer), longer);
     }
   };
   consider(kExtendRows, whole);
-  if (whole.parts <= 2 * num_cus) consider(kExtendSmallRows, totals(kExtendSmallRows, INT32_MAX));
+  if (whole.parts <= 2 * num_cus) {
+    measure(kExtendSmallRows);
+    consider(kExtendSmallRows, totals(INT32_MAX));
+  }
   return best;
 }
 
@@ -233,14 +275,28 @@ sf_status sf::extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_len
   const Split split = choose_split(desc, lens, news, num_cus > 0 ? num_cus : kDefaultNumCus);
   const int32_t rows = split.rows, most = split.most;
   const int32_t per = rows / g;
-  auto parts_of = [&](int32_t steps) { return (int64_t(steps) + most - 1) / most; };
+  auto parts_of = [&](int32_t steps) { return steps <= most ? 1 : (steps - 1) / most + 1; };
+  // Calls f(first step, end step) for the k parts of a walk: part i ends at
+  // floor((i + 1) steps / k), stepped forward without divisions.
+  auto each_cut = [](int32_t steps, int32_t k, auto f) {
+    const int32_t q = k > 1 ? steps / k : steps, rem = k > 1 ? steps % k : 0;
+    for (int32_t i = 0, b = 0, over = 0; i < k; ++i) {
+      int32_t e = b + q;
+      if ((over += rem) >= k) {
+        over -= k;
+        ++e;
+      }
+      f(b, e);
+      b = e;
+    }
+  };
   int64_t parts = 0, merges = 0, slots = 0, longest = 0;
   for_blocks(desc, lens, news, per, [&](int32_t, int32_t, int32_t, int32_t steps) {
-    const int64_t k = parts_of(steps);
-    parts += k * hkv;
+    const int32_t k = parts_of(steps);
+    parts += int64_t(k) * hkv;
     if (k > 1) {
       merges += hkv;
-      slots += k * hkv;
+      slots += int64_t(k) * hkv;
     }
     longest = std::max<int64_t>(longest, (steps + k - 1) / k);
   });
@@ -269,26 +325,25 @@ sf_status sf::extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_len
     int64_t qrow0 = 0;
     for_blocks(desc, lens, news, per, [&](int32_t s, int32_t t0, int32_t nt, int32_t steps) {
       for (; s_prev < s; ++s_prev) qrow0 += news[s_prev];
-      const int64_t k = parts_of(steps);
+      const int32_t k = parts_of(steps);
       for (int32_t h = 0; h < hkv; ++h) f(s, h, lens[s] - news[s] + t0, nt, int32_t(qrow0 + t0), steps, k);
     });
   };
-  each_part([&](int32_t, int32_t, int32_t, int32_t, int32_t, int32_t steps, int64_t k) {
-    for (int64_t i = 0; i < k; ++i) ++at[size_t(longest - ((i + 1) * steps / k - i * steps / k)) + 1];
+  for_blocks(desc, lens, news, per, [&](int32_t, int32_t, int32_t, int32_t steps) {
+    each_cut(steps, parts_of(steps), [&](int32_t b, int32_t e) { at[size_t(longest - (e - b)) + 1] += hkv; });
   });
   for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
   int32_t slot = 0, merge = 0;
   int32_t* merge_rows = work + parts * kItemInts;
-  each_part([&](int32_t s, int32_t h, int32_t first, int32_t nt, int32_t qrow, int32_t steps, int64_t k) {
+  each_part([&](int32_t s, int32_t h, int32_t first, int32_t nt, int32_t qrow, int32_t steps, int32_t k) {
     if (k > 1) {
-      const int32_t m8[kItemInts] = {slot, int32_t(k), nt, qrow, h, 0, 0, 0};
+      const int32_t m8[kItemInts] = {slot, k, nt, qrow, h, 0, 0, 0};
       std::memcpy(merge_rows + int64_t(merge++) * kItemInts, m8, sizeof m8);
     }
-    for (int64_t i = 0; i < k; ++i) {
-      const int32_t b = int32_t(i * steps / k), e = int32_t((i + 1) * steps / k);
+    each_cut(steps, k, [&](int32_t b, int32_t e) {
       const int32_t r8[kItemInts] = {s, h, b, nt, first, qrow, e, k > 1 ? ++slot : 0};
       std::memcpy(work + int64_t(at[size_t(longest - (e - b))]++) * kItemInts, r8, sizeof r8);
-    }
+    });
   });
   if (store) {
     int32_t* r = merge_rows + merges * kItemInts;
