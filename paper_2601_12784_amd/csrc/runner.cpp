@@ -45,6 +45,7 @@ struct Pinned {
   uint64_t bytes = 0;
   uint64_t last_step = 0;          // the step that last read it
   bool used = false;
+  bool in_arena = false;           // part of sf_runner::arena, not an allocation of its own
 };
 
 // An event recorded on one stream after steps [begin, end), all on that stream.
@@ -74,6 +75,7 @@ struct sf_runner {
   sf_plan_opts opts;
   int device = 0;
   Pinned ring[kRing];
+  void* arena = nullptr;   // one allocation that sf_runner_reserve cut into slots
   Mark marks[kMarks];
   uint64_t num_marks = 0;  // marks recorded so far (the next one reuses marks[num_marks % kMarks])
   uint64_t unmarked = 0;   // steps [unmarked, steps) have no mark yet
@@ -126,7 +128,8 @@ sf_status wait_all(sf_runner* r) {
 // Called only when no step in flight reads the slot (its last step has ended).
 sf_status grow_pinned(Pinned& p, uint64_t bytes) {
   if (p.bytes >= bytes) return SF_OK;
-  if (p.ptr && hipHostFree(p.ptr) != hipSuccess) return SF_ERR_HIP;
+  if (p.ptr && !p.in_arena && hipHostFree(p.ptr) != hipSuccess) return SF_ERR_HIP;
+  p.in_arena = false;
   p.ptr = nullptr;
   p.dev = nullptr;
   p.bytes = 0;
@@ -224,7 +227,8 @@ extern "C" void sf_runner_destroy(sf_runner* r) {
     if (m.ev) (void)hipEventDestroy(m.ev);
   }
   for (auto& p : r->ring)
-    if (p.ptr) (void)hipHostFree(p.ptr);
+    if (p.ptr && !p.in_arena) (void)hipHostFree(p.ptr);
+  if (r->arena) (void)hipHostFree(r->arena);
   if (r->workspace) {
     (void)hipDeviceSynchronize();
     (void)hipFree(r->workspace);
@@ -450,12 +454,33 @@ extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, u
   // An appending step also keeps its new-page array (padded to 32 bytes) and
   // copies of at most one 32-byte row per row of the work list in the slot.
   const uint64_t pages = (uint64_t(max_num_seqs) * 4 + 31) / 32 * 32;
-  const uint64_t slot = work_bytes + pages + work_bytes;
-  for (auto& p : r->ring) {
-    if (p.bytes >= slot) continue;
-    if (p.used && (st = wait_step(r, p.last_step)) != SF_OK) return st;
-    p.used = false;
-    if ((st = grow_pinned(p, slot)) != SF_OK) return st;
+  const uint64_t slot = (work_bytes + pages + work_bytes + 4095) / 4096 * 4096;
+  bool small = false;
+  for (auto& p : r->ring) small = small || p.bytes < slot;
+  if (!small) return SF_OK;
+  // The slots that are too small come from one allocation (32 of their own take
+  // 30 us each), once no step in flight reads the old ones. A slot leaves an
+  // arena only for more bytes than the arena's slots have, so where any slot is
+  // too small, all of an earlier arena's are.
+  if ((st = wait_all(r)) != SF_OK) return st;
+  void* ptr = nullptr;
+  void* dev = nullptr;
+  if (hipHostMalloc(&ptr, slot * kRing, hipHostMallocDefault) != hipSuccess) return SF_ERR_HIP;
+  if (hipHostGetDevicePointer(&dev, ptr, 0) != hipSuccess) {
+    (void)hipHostFree(ptr);
+    return SF_ERR_HIP;
   }
-  return SF_OK;
+  for (int i = 0; i < kRing; ++i) {
+    Pinned& p = r->ring[i];
+    if (p.bytes >= slot) continue;
+    if (p.ptr && !p.in_arena && hipHostFree(p.ptr) != hipSuccess) st = SF_ERR_HIP;
+    p = Pinned{};
+    p.ptr = reinterpret_cast<int32_t*>(static_cast<char*>(ptr) + slot * i);
+    p.dev = reinterpret_cast<const int32_t*>(static_cast<const char*>(dev) + slot * i);
+    p.bytes = slot;
+    p.in_arena = true;
+  }
+  if (r->arena && hipHostFree(r->arena) != hipSuccess) st = SF_ERR_HIP;
+  r->arena = ptr;
+  return st;
 }
