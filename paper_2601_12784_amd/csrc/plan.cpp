@@ -578,6 +578,15 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   return SF_OK;
 }
 
+// Up to 4 workers per CU while the batch has no more pairs than that, 8 above
+// (or where a workgroup's waves share a segment: then half as many segments).
+sf::PairPlanMost sf::pair_plan_most(const sf_attn_desc* shape, const sf_plan_opts* opts, int32_t num_seqs) {
+  const int64_t cus = opts && opts->num_cus > 0 ? opts->num_cus : kDefaultNumCus;
+  const int64_t pairs = int64_t(num_seqs) * shape->num_kv_heads;
+  const int64_t segments = pairs > 4 * cus ? 8 * cus : 4 * cus;
+  return {segments, 8 * cus + segments + std::min(pairs, segments / 2)};
+}
+
 extern "C" sf_status sf_runner_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts,
                                     int32_t kind, int32_t* work_host, uint64_t work_capacity_bytes,
                                     sf_plan_info* info) {

@@ -440,11 +440,14 @@ extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, u
                                        int32_t max_num_seqs, void* stream) {
   if (!r || max_num_seqs < 0) return SF_ERR_INVALID_ARG;
   hipStream_t main = static_cast<hipStream_t>(stream);
-  // Smaller batches than the one reserved for may be planned as whole segments
-  // of pairs, one per worker, up to four workers per CU of them partial.
-  const int64_t cus = r->opts.num_cus > 0 ? r->opts.num_cus : sf::kDefaultNumCus;
-  const uint64_t head_rows = uint64_t(4 * cus) * (r->shape.num_q_heads / r->shape.num_kv_heads);
+  // Smaller batches than the one reserved for may be planned as segments of
+  // pairs, which take other shares of the memory: up to most.partials, and up
+  // to most.rows (a batch with rows for a quarter of that or less has too few
+  // pages to come near it: four times its own rows then).
+  const sf::PairPlanMost most = sf::pair_plan_most(&r->shape, &r->opts, max_num_seqs);
+  const uint64_t head_rows = uint64_t(most.partials) * (r->shape.num_q_heads / r->shape.num_kv_heads);
   workspace_bytes = std::max(workspace_bytes, sf::align256(head_rows * r->shape.head_dim * 4) + sf::align256(head_rows * 4));
+  work_bytes = std::max(work_bytes, std::min(uint64_t(most.rows) * sf::kItemInts * 4, 4 * work_bytes));
   // partials, then the device copy of the merge rows (at most the work
   // list's size) and new_pages
   sf_status st = grow_device(r, &r->workspace, &r->workspace_bytes,

@@ -116,3 +116,25 @@ def test_shared_groups_are_the_runners_alone():
     fake = 1 << 20
     assert B.lib().sf_decode_attn(ctypes.byref(desc), ctypes.byref(info), None, fake, fake, fake, fake, fake, fake, None, fake,
                                   1 << 30, None) == 4
+
+
+def test_smaller_batches_fit_what_a_large_one_reserves():
+    """sf_runner_reserve's floor, re-derived: segments of pairs take at most 4 per
+    CU (8 where the pairs alone are more than 4 per CU) and 8 workers per CU,
+    whatever the batch; its four times the reserved rows covers every batch that
+    the reserved one shrinks to."""
+    rng = np.random.default_rng(3)
+    cus = 256
+    for trial in range(200):
+        hkv = int(rng.choice([1, 2, 4, 8]))
+        n = int(rng.choice([1, 3, 17, 64, 140, 200, 520, 1030]))
+        full = rng.integers(1, int(rng.choice([40, 600, 4000, 20000])), n)
+        _, large, _ = runner_plan(full, 4 * hkv, hkv, 128)
+        for _ in range(4):
+            lens = np.minimum(full, rng.integers(0, full.max() + 1, n) if rng.random() < .5 else rng.integers(1, full.max() + 1))
+            lens = rng.permutation(lens)[: int(rng.integers(1, n + 1))]
+            _, info, _ = runner_plan(lens, 4 * hkv, hkv, 128)
+            segments = 8 * cus if n * hkv > 4 * cus else 4 * cus
+            rows = 8 * cus + segments + min(n * hkv, segments // 2)
+            assert info.work_bytes <= max(large.work_bytes, min(rows * 32, 4 * large.work_bytes)), (trial, lens)
+            assert info.num_partials <= max(large.num_partials, segments), (trial, lens)
