@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "sf_internal.h"
@@ -422,8 +423,13 @@ extern "C" sf_status sf_debug_extend_plan(const sf_attn_desc* desc, const int32_
   if (!counts || num_cus < 0 || (work_capacity_bytes > 0 && !work_host)) return SF_ERR_INVALID_ARG;
   ExtendPlan plan = {};
   sf_extend_info info;
-  const sf_status st = extend_plan_parts(desc, seq_lens_host, q_lens_host, num_cus, store != 0, work_host,
-                                         work_capacity_bytes, &plan, &info);
+  sf_status st = SF_OK;
+  try {
+    st = extend_plan_parts(desc, seq_lens_host, q_lens_host, num_cus, store != 0, work_host, work_capacity_bytes, &plan,
+                           &info);
+  } catch (const std::bad_alloc&) {
+    return SF_ERR_HIP;
+  }
   const int32_t c[5] = {plan.rows, plan.num_parts, plan.num_merge, plan.num_store, plan.num_slots};
   std::memcpy(counts, c, sizeof c);
   return st;
