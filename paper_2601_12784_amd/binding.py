@@ -451,7 +451,9 @@ class ExtendAttention:
     runner. A stream that is being captured into a graph takes sf_extend_attn
     instead, on a work list that is uploaded with the launch; before that list
     is rewritten, the call waits for the event recorded after the previous
-    upload."""
+    upload. Pinned memory can't be allocated during a capture, so an eager call
+    keeps room for its own batch's list: one that is captured after it allocates
+    nothing."""
 
     def __init__(self, num_q_heads, num_kv_heads, head_dim, device=None):
         self.hq, self.hkv, self.d = int(num_q_heads), int(num_kv_heads), int(head_dim)
@@ -460,6 +462,7 @@ class ExtendAttention:
         self._runner = ctypes.c_void_p()
         self._memory = sf_runner_memory()
         self._lent = None
+        self._spare = None
         self._work_host = None
         self._work_dev = None
         self._uploaded = None
@@ -480,9 +483,12 @@ class ExtendAttention:
         need = int(m.need_slot)
         slots = 32 if need <= 1 << 14 else 8 if need <= 1 << 18 else 4
         slot = max(int(m.pinned_bytes) // m.slots if m.slots else 0, (need + need // 4 + 1023) // 32 * 32)
-        device = max(int(m.device_bytes), int(m.need_device) * 5 // 4 + 4096)
-        pinned = torch.empty(slots * slot, dtype=torch.uint8, pin_memory=True)
-        work = torch.empty(device, dtype=torch.uint8, device=self.device)
+        device = (max(int(m.device_bytes), int(m.need_device) * 5 // 4 + 4096) + 255) // 256 * 256
+        # One slot more, on both sides, for a captured call: sf_extend_attn's
+        # list has at most a row for each of the runner's.
+        pinned = torch.empty((slots + 1) * slot, dtype=torch.uint8, pin_memory=True)
+        work = torch.empty(device + slot, dtype=torch.uint8, device=self.device)
+        self._spare = (pinned[slots * slot:].view(torch.int32), work[device:].view(torch.int32))
         if stream is not None:   # the allocation is ordered on the current stream
             torch.cuda.current_stream(self.device).synchronize()
         m.pinned, m.pinned_bytes, m.slots = pinned.data_ptr(), slots * slot, slots
@@ -496,14 +502,18 @@ class ExtendAttention:
         if lens.ndim != 1 or lens.shape != qls.shape:
             raise ValueError("seq_lens and q_lens must have num_seqs entries")
         desc = make_desc(lens.size, self.hq, self.hkv, self.d, block_table.shape[1], k_pool.shape[0], scale)
-        if self._L is None:
-            self._create()
         rows = int(qls.sum())
         if DEBUG_CHECKS:
             check_block_table(desc, block_table, np.where(qls > 0, lens, 0))
         if out is None:
             out = torch.empty((rows, self.hq, self.d), dtype=torch.float32, device=self.device)
         _check_extend(desc, rows, q, k_pool, v_pool, block_table, out, lse, k_new, v_new)
+        if self._L is None:
+            if torch.cuda.is_current_stream_capturing():   # a runner's events are not created in a capture
+                self.last_info = self._call_captured(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new,
+                                                     v_new, stream)
+                return out
+            self._create()
         info = sf_extend_info()
         args = (self._runner, ctypes.byref(desc), _host_addr(lens), _host_addr(qls), q.data_ptr(), _addr(k_new),
                 _addr(v_new), k_pool.data_ptr(), v_pool.data_ptr(), block_table.data_ptr(), out.data_ptr(), _addr(lse),
@@ -528,8 +538,11 @@ class ExtendAttention:
         if self._uploaded is not None:
             self._uploaded.synchronize()
         if self._work_host is None or self._work_host.numel() < need:
-            self._work_host = torch.empty(need, dtype=torch.int32, pin_memory=True)
-            self._work_dev = torch.empty(need, dtype=torch.int32, device=self.device)
+            if self._spare is not None and self._spare[0].numel() >= need:
+                self._work_host, self._work_dev = self._spare   # kept as long as this object, as a graph reads them
+            else:
+                self._work_host = torch.empty(need, dtype=torch.int32, pin_memory=True)
+                self._work_dev = torch.empty(need, dtype=torch.int32, device=self.device)
         info, _ = sf_extend_attn_plan(desc, lens, qls, work_host=self._work_host)
         sf_extend_attn(desc, info, self._work_host, self._work_dev, q, k_pool, v_pool, block_table, out, lse,
                        k_new=k_new, v_new=v_new, stream=stream)

@@ -123,3 +123,37 @@ def test_captured_stream_is_left_to_the_plain_entry_point():
     graph.replay()
     torch.cuda.synchronize()
     assert st == B.UNSUPPORTED and torch.equal(out, before + 1.0)
+
+
+@pytest.mark.parametrize("lens,qls", [([60], [60]), ([3000, 700, 40], [300, 700, 1])])
+def test_call_after_a_warm_one_is_captured(lens, qls):
+    """A captured call allocates no pinned memory after an eager one over the same
+    batch, and its graph keeps its own work list: replays with other eager calls
+    of the object between them all give the eager result of the whole items."""
+    eb, other = build_extend(lens, qls, 28, 4, 128, seed=4), build_extend([9000], [700], 28, 4, 128, seed=9)
+    b, c = eb.batch, other.batch
+    args = (eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens, eb.q_lens,
+            b.scale)
+    args2 = (other.q.cuda(), c.k_pool.cuda(), c.v_pool.cuda(), torch.from_numpy(c.block_table).cuda(), c.seq_lens,
+             other.q_lens, c.scale)
+    out = torch.zeros((int(sum(qls)), 28, 128), dtype=torch.float32, device="cuda")
+    desc = B.make_desc(len(lens), 28, 4, 128, b.block_table.shape[1], b.num_pages, b.scale)
+    info, work = B.sf_extend_attn_plan(desc, b.seq_lens, eb.q_lens)
+    want = torch.zeros_like(out)
+    B.sf_extend_attn(desc, info, None, torch.from_numpy(work).cuda(), *args[:4], want)
+    call = B.ExtendAttention(28, 4, 128)
+    call(*args, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(*args, out=out)
+    first = None
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        again = call(*args2)   # outgrows the lent memory
+        torch.cuda.synchronize()
+        first = again if first is None else first
+        assert torch.equal(again, first)
