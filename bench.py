@@ -374,7 +374,7 @@ def routing_demo(k1_per_token, mu=0.3, seed=0):
             "sf_route_us": round(us, 1)}
 
 
-EXTEND_KERNEL = "extend_attn_kernel<128>"
+EXTEND_KERNEL = "extend_attn_kernel<128, 12>"
 EXTEND_SRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2601_12784_amd", "csrc",
                           "extend_attn.hip")
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 matrix peak
@@ -556,7 +556,7 @@ def stored_traffic(kv_bytes_per_launch):
 
 
 # the long-tail launch: head_dim 128, no append, 4 waves (workers) per workgroup
-ATTN_KERNEL = "attn_worker_kernel<128, false, 4>"
+ATTN_KERNEL = "attn_worker_kernel<128, false, 4, false>"
 COMBINE_KERNEL = "combine_kernel"
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
