@@ -481,7 +481,7 @@ class ExtendAttention:
         stays alive until the next call has waited for the steps that use it."""
         m = self._memory
         need = int(m.need_slot)
-        slots = 32 if need <= 1 << 14 else 8 if need <= 1 << 18 else 4
+        slots = 31 if need <= 1 << 14 else 7 if need <= 1 << 18 else 4
         slot = max(int(m.pinned_bytes) // m.slots if m.slots else 0, (need + need // 4 + 1023) // 32 * 32)
         device = (max(int(m.device_bytes), int(m.need_device) * 5 // 4 + 4096) + 255) // 256 * 256
         # One slot more, on both sides, for a captured call: sf_extend_attn's
