@@ -426,7 +426,11 @@ sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info, c
  * sf_extend_attn; the runner's own plan differs from sf_extend_attn_plan's
  * where that one would leave compute units idle: items of 128 rows instead of
  * 384, and key walks cut into parts whose partial results a further launch
- * merges. *info is what sf_extend_attn_plan reports for the same lengths.
+ * merges. Which walks are cut depends on the whole batch; a cut walk's results
+ * differ from the whole walk's (and so from sf_extend_attn's) by fp32 rounding,
+ * about 1e-6 relative, except in rows whose scores rise by more than 12 log2
+ * units over those of the first 32 keys, where fp16 rounding of the weights may
+ * fall differently. *info is what sf_extend_attn_plan reports for the same lengths.
  *
  * The call allocates nothing: *memory lends it pinned host memory (16-byte
  * aligned, `slots` <= 32 equal slots of whole 32-byte rows, one plan each) and

@@ -158,6 +158,14 @@ __device__ __forceinline__ float weight_sum(const float* p) {
 // and O and l are rescaled; every weight is then at most 1, so the check
 // stays quiet until a row's scores rise more than 12 (log2 units) above its
 // reference. Key 0 is in every row's first step, so m is finite after it.
+//
+// A part of a walk that starts later takes its rows' first reference from the
+// walk's step 0 all the same, so that its weights are rounded to fp16 as the
+// whole walk rounds them: cut or whole, with whatever neighbours in the batch,
+// a row's result differs by the merge's fp32 rounding alone (until a row's
+// scores rise past the headroom; a part does not see moves before its start).
+// With a reference of its own from the part's first step the results differed
+// by 2.4e-4 (4 x 256 tokens after 8000), at the same error against 64 bits.
 struct TileWeights {
   float sc[8];   // raw scores of this lane (masked ones -inf)
   float p[8];    // 2^(sc * c - m)
@@ -166,12 +174,10 @@ struct TileWeights {
   bool need;     // the sum exceeds the headroom (or is inf / NaN)
 };
 
-// Part 1: exponentiate against the current reference. s0 / s1: this lane's
-// scores for keys key0 + 4*grp + e of the step's two pages.
+// This lane's scores s0 / s1, for keys key0 + 4*grp + e of a step's two pages.
 template <bool kMasked>
-__device__ __forceinline__ TileWeights exponentiate(const f32x4& s0, const f32x4& s1, int key0, int grp, int limit,
-                                                    float c, float m) {
-  TileWeights t;
+__device__ __forceinline__ void take_scores(TileWeights& t, const f32x4& s0, const f32x4& s1, int key0, int grp,
+                                            int limit) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     t.sc[e] = s0[e];
@@ -184,6 +190,24 @@ __device__ __forceinline__ TileWeights exponentiate(const f32x4& s0, const f32x4
       t.sc[e] = t.ok[e] ? t.sc[e] : -__builtin_inff();
     }
   }
+}
+
+// Raw row maximum of a step, in every lane of the row. The scale is >= 0 (the
+// host flips the query's sign for a negative one), so it gives the max of the
+// scaled scores.
+__device__ __forceinline__ float row_max(const TileWeights& t) {
+  float mx = fmaxf(fmaxf(fmaxf(t.sc[0], t.sc[1]), fmaxf(t.sc[2], t.sc[3])),
+                   fmaxf(fmaxf(t.sc[4], t.sc[5]), fmaxf(t.sc[6], t.sc[7])));
+  mx = fmaxf(mx, __shfl_xor(mx, 16));
+  return fmaxf(mx, __shfl_xor(mx, 32));
+}
+
+// Part 1: exponentiate against the current reference.
+template <bool kMasked>
+__device__ __forceinline__ TileWeights exponentiate(const f32x4& s0, const f32x4& s1, int key0, int grp, int limit,
+                                                    float c, float m) {
+  TileWeights t;
+  take_scores<kMasked>(t, s0, s1, key0, grp, limit);
 #pragma unroll
   for (int e = 0; e < 8; ++e) t.p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(t.sc[e], c, -m));
   t.part = weight_sum(t.p);
@@ -198,17 +222,10 @@ __device__ __forceinline__ TileWeights exponentiate(const f32x4& s0, const f32x4
 template <int D, bool kMasked>
 __device__ __forceinline__ u32x4 settle(TileWeights& t, float c, float& m, float& lsum, f32x4* o) {
   if (__any(t.need)) {
-    // The scale c is >= 0 (the host flips the query's sign for a negative
-    // one), so the row max of the raw scores gives the max of the scaled ones.
-    float mx = fmaxf(fmaxf(fmaxf(t.sc[0], t.sc[1]), fmaxf(t.sc[2], t.sc[3])),
-                     fmaxf(fmaxf(t.sc[4], t.sc[5]), fmaxf(t.sc[6], t.sc[7])));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mx_s = mx * c;
+    const float mx_s = row_max(t) * c;
     const bool grow = mx_s > m;   // NaN (fully masked, zero scale) compares false
     const float mnew = grow ? mx_s : m;
-    // (a part of a walk may hold no key of a row at all: m stays -inf)
-    const float alpha = mnew == -__builtin_inff() ? 1.f : __builtin_amdgcn_exp2f(m - mnew);
+    const float alpha = __builtin_amdgcn_exp2f(m - mnew);
     m = mnew;
     lsum *= alpha;
 #pragma unroll
@@ -245,8 +262,9 @@ void extend_attn_kernel(ExtendArgs a) {
   const int kvh = item[1];
   const int nt = item[3];
   // Whole items: steps [0, item[6]) of the block that starts at new token
-  // item[2]. Parts of items (kExtendPart*): steps [item[2], item[6]), with the
-  // block's first position and first query row in place of the sequence's.
+  // item[2]. Parts of items (ExtendPlan's part rows): steps [item[2], item[6]),
+  // with the block's first position and first query row in place of the
+  // sequence's.
   const int t0 = a.parts ? 0 : item[2];
   const int begin = a.parts ? item[2] : 0;
   const int prefix = item[4];
@@ -378,8 +396,7 @@ void extend_attn_kernel(ExtendArgs a) {
   // One step, operands read from LDS just before use: the scores of both
   // row tiles per 32 dims of K, then the softmax of both, then P.V per
   // 16 dims of V (the third wave on each SIMD hides the latencies).
-  auto compute = [&](const uint16_t* L, int key0) {
-    f32x4 s0[kRowTiles], s1[kRowTiles];
+  auto scores = [&](const uint16_t* L, f32x4* s0, f32x4* s1) {
 #pragma unroll
     for (int rt = 0; rt < kRowTiles; ++rt) {
       s0[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -396,6 +413,10 @@ void extend_attn_kernel(ExtendArgs a) {
         s1[rt] = mfma_bf16(k1, qf[rt][kb], s1[rt]);
       }
     }
+  };
+  auto compute = [&](const uint16_t* L, int key0) {
+    f32x4 s0[kRowTiles], s1[kRowTiles];
+    scores(L, s0, s1);
     const int vo = 2 * TE + col * 32 + (grp ^ v_swizzle(col)) * 8;
     auto tail = [&](auto masked_tag) {
       constexpr bool kMasked = decltype(masked_tag)::value;
@@ -419,11 +440,27 @@ void extend_attn_kernel(ExtendArgs a) {
   };
 
   if (stager) {
+    const bool first = begin > 0 && stile < 2;   // the keys of step 0, for a later part's reference
+    u32x4 k0[NC];
+    if (first) fetch(k0, 0);
     fetch(pre[0], begin);
     if constexpr (kAhead == 2) fetch(pre[1], begin + 1);
+    if (first) stage(lds[1], k0, 0);
     stage(lds[0], pre[0], begin);
   }
   __syncthreads();
+  if (begin > 0) {
+    f32x4 s0[kRowTiles], s1[kRowTiles];
+    scores(lds[1], s0, s1);
+#pragma unroll
+    for (int rt = 0; rt < kRowTiles; ++rt) {
+      TileWeights t;
+      take_scores<true>(t, s0[rt], s1[rt], 0, grp, limit[rt]);
+      const float mx_s = row_max(t) * c;
+      m[rt] = mx_s > m[rt] ? mx_s : m[rt];   // as settle() moves it
+    }
+    __syncthreads();   // before the next step is staged over these keys
+  }
 
   // One step from buffer `cur` while the next is staged into `nxt` and, two
   // ahead, the one after it is fetched; the loop is unrolled by two so that
