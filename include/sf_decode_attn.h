@@ -435,12 +435,13 @@ sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info, c
  * The call allocates nothing: *memory lends it pinned host memory (16-byte
  * aligned, `slots` <= 32 equal slots of whole 32-byte rows, one plan each) and
  * device memory, both the caller's and unchanged until the runner is
- * destroyed or a call passes other memory (which first waits for the steps so
+ * destroyed or a call passes other memory (which first waits for the calls so
  * far). If a slot or the device memory is too small the call launches
  * nothing, writes the bytes it needs to need_slot and need_device and returns
  * SF_ERR_CAPACITY. Calls on one runner must not overlap on the host; a call on
- * another stream than the runner's last step waits for the steps so far.
- * Asynchronous on stream. Other errors as sf_extend_attn_plan and
+ * another stream than the runner's last extend call waits for its calls so far.
+ * Nothing is recorded on a stream after the call it was given to, so it may be
+ * destroyed between calls. Asynchronous on stream. Other errors as sf_extend_attn_plan and
  * sf_extend_attn; SF_ERR_UNSUPPORTED, with nothing launched, also on a stream
  * that is being captured into a graph.
  */

@@ -44,6 +44,7 @@
 // of 128 rows double the K/V staging per row and are 2x slower; 16 rows per
 // wave (16 waves, four per SIMD) doubles the LDS operand reads per row and
 // is 12 % slower than three waves of 32 rows.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -683,34 +684,44 @@ __global__ __launch_bounds__(kStoreThreads) void extend_rows_kernel(ExtendArgs a
   if (i < a.copy_ints) a.copy_dst[i] = a.copy_src[i];
 }
 
-}  // namespace
-
-template <int D>
-hipError_t launch_extend_d(const ExtendArgs& a, hipStream_t stream) {
-  if (a.num_store > 0) {
-    hipLaunchKernelGGL(kv_store_pages_kernel<D>, dim3(a.num_store), dim3(kStoreThreads), 0, stream, a);
-  } else if (a.k_new) {
-    hipLaunchKernelGGL(kv_store_kernel<D>, dim3(a.num_items), dim3(kStoreThreads), 0, stream, a);
-  } else if (a.copy_ints > 0) {
-    hipLaunchKernelGGL(extend_rows_kernel, dim3((a.copy_ints + kStoreThreads - 1) / kStoreThreads),
-                       dim3(kStoreThreads), 0, stream, a);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.parts && a.part_rows == kExtendSmallRows)
-    hipLaunchKernelGGL((extend_attn_kernel<D, 4>), dim3(a.num_items), dim3(256), 0, stream, a);
+// The event comes with the last launch itself: recording it after the call
+// would put a marker between one call's last launch and the next call's first.
+template <class Kernel>
+hipError_t launch(Kernel kernel, dim3 grid, dim3 block, hipStream_t stream, hipEvent_t done, const ExtendArgs& a) {
+  if (done)
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, nullptr, done, 0, a);
   else
-    hipLaunchKernelGGL((extend_attn_kernel<D, 12>), dim3(a.num_items), dim3(768), 0, stream, a);
-  if ((e = hipGetLastError()) != hipSuccess || a.num_merge == 0) return e;
-  constexpr int kRowsPerBlock = kMergeThreads / (D / 4);
-  hipLaunchKernelGGL(extend_merge_kernel<D>, dim3(a.num_merge, (a.part_rows + kRowsPerBlock - 1) / kRowsPerBlock),
-                     dim3(kMergeThreads), 0, stream, a);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 
-hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream) {
+template <int D>
+hipError_t launch_extend_d(const ExtendArgs& a, hipStream_t stream, hipEvent_t done) {
+  hipError_t e = hipSuccess;
+  if (a.num_store > 0)
+    e = launch(kv_store_pages_kernel<D>, dim3(a.num_store), dim3(kStoreThreads), stream, nullptr, a);
+  else if (a.k_new)
+    e = launch(kv_store_kernel<D>, dim3(a.num_items), dim3(kStoreThreads), stream, nullptr, a);
+  else if (a.copy_ints > 0)
+    e = launch(extend_rows_kernel, dim3((a.copy_ints + kStoreThreads - 1) / kStoreThreads), dim3(kStoreThreads), stream,
+               nullptr, a);
+  if (e != hipSuccess) return e;
+  const hipEvent_t attention_done = a.num_merge > 0 ? nullptr : done;
+  if (a.parts && a.part_rows == kExtendSmallRows)
+    e = launch(extend_attn_kernel<D, 4>, dim3(a.num_items), dim3(256), stream, attention_done, a);
+  else
+    e = launch(extend_attn_kernel<D, 12>, dim3(a.num_items), dim3(768), stream, attention_done, a);
+  if (e != hipSuccess || a.num_merge == 0) return e;
+  constexpr int kRowsPerBlock = kMergeThreads / (D / 4);
+  return launch(extend_merge_kernel<D>, dim3(a.num_merge, (a.part_rows + kRowsPerBlock - 1) / kRowsPerBlock),
+                dim3(kMergeThreads), stream, done, a);
+}
+
+}  // namespace
+
+hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, hipEvent_t done) {
   if (a.num_items == 0) return hipSuccess;
-  return a.head_dim == 128 ? launch_extend_d<128>(a, stream) : launch_extend_d<64>(a, stream);
+  return a.head_dim == 128 ? launch_extend_d<128>(a, stream, done) : launch_extend_d<64>(a, stream, done);
 }
 
 }  // namespace sf

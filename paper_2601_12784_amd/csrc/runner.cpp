@@ -55,7 +55,9 @@ struct Mark {
   bool valid = false;
 };
 
-// Memory lent by sf_runner_extend's caller.
+// Memory lent by sf_runner_extend's caller. Each slot has an event that the
+// call's last launch completes: nothing is recorded on a stream after the call
+// that was given it, so the caller may destroy it between calls.
 struct Lent {
   void* pinned = nullptr;
   const char* pinned_dev = nullptr;   // the same memory as the kernels address it
@@ -64,8 +66,9 @@ struct Lent {
   void* device = nullptr;
   uint64_t device_bytes = 0;
   uint64_t next = 0;                  // slots go round
-  uint64_t last_step[kRing] = {};     // the step that last read the slot
-  bool used[kRing] = {};
+  hipEvent_t done[kRing] = {};        // created with the slot's first call
+  bool used[kRing] = {};              // a call whose end has not been waited for read the slot
+  hipStream_t last_stream = nullptr;  // of the last call (compared, never used)
 };
 
 }  // namespace
@@ -163,20 +166,18 @@ sf_status grow_device(sf_runner* r, void** ptr, uint64_t* have, uint64_t bytes, 
   return SF_OK;
 }
 
-// Counts a step whose launches (status st) may read its slot, and marks the
-// steps in their turn.
-sf_status finish_step(sf_runner* r, hipStream_t main, sf_status st, uint64_t mark_every) {
-  r->last_stream = main;
-  ++r->steps;
-  if (r->steps - r->unmarked >= mark_every && mark_steps(r) != SF_OK) {
-    // Without the mark nothing orders a later rewrite of these slots after
-    // the steps' reads: wait for the stream instead.
-    (void)hipStreamSynchronize(main);
-    for (auto& p : r->ring) p.used = false;
-    for (auto& u : r->lent.used) u = false;
-    r->unmarked = r->steps;
-    if (st == SF_OK) st = SF_ERR_HIP;
-  }
+// Returns once the call that last read the lent slot has ended.
+sf_status wait_slot(Lent& l, int slot) {
+  if (l.used[slot] && hipEventSynchronize(l.done[slot]) != hipSuccess) return SF_ERR_HIP;
+  l.used[slot] = false;
+  return SF_OK;
+}
+
+// Returns once every call on the lent memory has ended.
+sf_status wait_lent(Lent& l) {
+  sf_status st = SF_OK;
+  for (int i = 0; i < kRing; ++i)
+    if (wait_slot(l, i) != SF_OK) st = SF_ERR_HIP;
   return st;
 }
 
@@ -226,6 +227,9 @@ extern "C" void sf_runner_destroy(sf_runner* r) {
     if (m.ev && m.valid) (void)hipEventSynchronize(m.ev);
     if (m.ev) (void)hipEventDestroy(m.ev);
   }
+  (void)wait_lent(r->lent);
+  for (auto ev : r->lent.done)
+    if (ev) (void)hipEventDestroy(ev);
   for (auto& p : r->ring)
     if (p.ptr && !p.in_arena) (void)hipHostFree(p.ptr);
   if (r->arena) (void)hipHostFree(r->arena);
@@ -333,7 +337,17 @@ extern "C" sf_status sf_runner_step(sf_runner* r, const sf_attn_desc* desc, cons
   }
   pin.used = true;
   pin.last_step = r->steps;
-  return finish_step(r, main, st, kMarkEvery);
+  r->last_stream = main;
+  ++r->steps;
+  if (r->steps - r->unmarked >= kMarkEvery && mark_steps(r) != SF_OK) {
+    // Without the mark nothing orders a later rewrite of these slots after
+    // the steps' reads: wait for the stream instead.
+    (void)hipStreamSynchronize(main);
+    for (auto& p : r->ring) p.used = false;
+    r->unmarked = r->steps;
+    if (st == SF_OK) st = SF_ERR_HIP;
+  }
+  return st;
 }
 
 // Extend attention, in memory that the caller lends: the pinned part is cut
@@ -362,22 +376,21 @@ extern "C" sf_status sf_runner_extend(sf_runner* r, const sf_attn_desc* desc, co
   const uint64_t slot_bytes = memory->slots > 0 ? memory->pinned_bytes / memory->slots / 32 * 32 : 0;
   if (lent.pinned != memory->pinned || lent.slots != memory->slots || lent.slot_bytes != slot_bytes ||
       lent.device != memory->device || lent.device_bytes != memory->device_bytes) {
-    if ((st = wait_all(r)) != SF_OK) return st;
+    if ((st = wait_lent(lent)) != SF_OK) return st;
     if (memory->slots < 0 || memory->slots > kRing || (memory->pinned == nullptr) != (memory->slots == 0))
       return SF_ERR_INVALID_ARG;
     void* dev = nullptr;
     if (memory->pinned && hipHostGetDevicePointer(&dev, memory->pinned, 0) != hipSuccess) return SF_ERR_HIP;
-    lent = Lent{};
     lent.pinned = memory->pinned;
     lent.pinned_dev = static_cast<const char*>(dev);
     lent.slots = memory->slots;
     lent.slot_bytes = slot_bytes;
     lent.device = memory->device;
     lent.device_bytes = memory->device_bytes;
+    lent.next = 0;
   }
   const int slot = lent.slots > 0 ? lent.next % lent.slots : 0;
-  if (lent.used[slot] && (st = wait_step(r, lent.last_step[slot])) != SF_OK) return st;
-  lent.used[slot] = false;
+  if ((st = wait_slot(lent, slot)) != SF_OK) return st;
 
   const bool store = k_new != nullptr;
   sf::ExtendPlan plan;
@@ -408,9 +421,15 @@ extern "C" sf_status sf_runner_extend(sf_runner* r, const sf_attn_desc* desc, co
   sf::ExtendArgs a;
   if ((st = sf::extend_args(desc, work_dev, q, k_new, v_new, k_pool, v_pool, block_table, out, lse, &a)) != SF_OK)
     return st;
-  // Steps of another stream may still use the device memory: they are waited
-  // for (steps on one stream are in order by themselves).
-  if (r->steps > 0 && main != r->last_stream && (st = wait_all(r)) != SF_OK) return st;
+  // Calls of another stream may still use the device memory: they are waited
+  // for (calls on one stream are in order by themselves).
+  if (main != lent.last_stream && (st = wait_lent(lent)) != SF_OK) return st;
+  // The slot's event skips HIP's system-scope fence, as the marks do.
+  if (!lent.done[slot] &&
+      hipEventCreateWithFlags(&lent.done[slot], hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+    lent.done[slot] = nullptr;
+    return SF_ERR_HIP;
+  }
   char* ws = static_cast<char*>(lent.device);
   a.parts = true;
   a.num_items = plan.num_parts;
@@ -427,13 +446,15 @@ extern "C" sf_status sf_runner_extend(sf_runner* r, const sf_attn_desc* desc, co
     a.items = a.copy_dst;
   }
   a.merge_rows = a.items + int64_t(plan.num_parts) * sf::kItemInts;
-  st = sf::launch_extend(a, main) == hipSuccess ? SF_OK : SF_ERR_HIP;
+  if (sf::launch_extend(a, main, lent.done[slot]) != hipSuccess) {
+    // An earlier launch of the call may read the slot, with no event behind it.
+    (void)hipStreamSynchronize(main);
+    return SF_ERR_HIP;
+  }
   lent.used[slot] = true;
-  lent.last_step[slot] = r->steps;
+  lent.last_stream = main;
   ++lent.next;
-  // every half round of slots is marked, so a slot's last step is marked
-  // before the slot comes round again
-  return finish_step(r, main, st, lent.slots > 1 ? lent.slots / 2 : 1);
+  return SF_OK;
 }
 
 extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, uint64_t work_bytes,

@@ -255,7 +255,8 @@ sf_status decode_attn_rows(const sf_attn_desc* desc, const sf_plan_info* info, i
                            const int32_t* block_table, float* out, float* lse, void* workspace,
                            uint64_t workspace_bytes, void* stream, const RowCopy* copy, void* attn_start,
                            void* attn_end, bool shared_groups = false);
-hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream);
+// done (may be NULL): an event that the call's last launch completes.
+hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, hipEvent_t done = nullptr);
 
 // Every host-side check of a decode step's arguments except the workspace
 // (k_new / v_new / new_pages: an appending step; k_scale / v_scale: fp8).

@@ -2,6 +2,8 @@
 one: key walks cut into parts, 128-row items, the page-wise store, and calls
 that queue up behind each other. Against the fp64 oracle at
 |gpu - ref| <= 2e-3 + 1e-2 |ref|; stores bit for bit."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -177,3 +179,39 @@ def test_call_after_a_warm_one_is_captured(lens, qls):
         torch.cuda.synchronize()
         first = again if first is None else first
         assert torch.equal(again, first)
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    with open("/proc/self/maps") as f:
+        path = next(x.split()[-1] for x in f if "libamdhip64" in x)
+    return ctypes.CDLL(path)
+
+
+def test_streams_that_end_between_calls():
+    """An object's calls on streams that their owner destroys afterwards: nothing
+    of an earlier call is recorded on its stream later, neither when the next
+    call comes on another stream, nor when a slot is used again, nor when the
+    lent memory grows."""
+    hip = _hip()
+    small, large = build_extend([300], [20], 28, 4, 128, seed=31), build_extend([6000], [700], 28, 4, 128, seed=32)
+    args = []
+    for eb in (small, large):
+        b = eb.batch
+        args.append((eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens,
+                     eb.q_lens, b.scale))
+    want = [B.ExtendAttention(28, 4, 128)(*x) for x in args]
+    torch.cuda.synchronize()
+    call = B.ExtendAttention(28, 4, 128)
+    for i, (which, calls) in enumerate([(0, 1), (0, 40), (1, 1), (0, 2), (1, 9)]):
+        h = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(h)) == 0
+        outs = [torch.empty_like(want[which]) for _ in range(calls)]
+        torch.cuda.synchronize()
+        for out in outs:
+            call(*args[which], out=out, stream=h.value)
+        assert hip.hipStreamSynchronize(h) == 0 and hip.hipStreamDestroy(h) == 0
+        for out in outs:
+            assert torch.equal(out, want[which]), f"stream {i}"
+    assert torch.equal(call(*args[0]), want[0])
+    torch.cuda.synchronize()
