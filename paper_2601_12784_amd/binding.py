@@ -449,11 +449,11 @@ class ExtendAttention:
     each other without waiting. The pinned slots and the device memory for
     partial results are torch tensors that this object keeps and lends to the
     runner. A stream that is being captured into a graph takes sf_extend_attn
-    instead, on a work list that is uploaded with the launch; before that list
-    is rewritten, the call waits for the event recorded after the previous
-    upload. Pinned memory can't be allocated during a capture, so an eager call
-    keeps room for its own batch's list: one that is captured after it allocates
-    nothing."""
+    instead, on a work list that the graph uploads at each replay. Captured
+    calls share a list only where it is the same; none is rewritten or freed
+    while the object lives, so the object must outlive the graphs. Pinned memory
+    can't be allocated during a capture, so an eager call keeps room for its own
+    batch's list: one that is captured after it allocates nothing."""
 
     def __init__(self, num_q_heads, num_kv_heads, head_dim, device=None):
         self.hq, self.hkv, self.d = int(num_q_heads), int(num_kv_heads), int(head_dim)
@@ -462,10 +462,8 @@ class ExtendAttention:
         self._runner = ctypes.c_void_p()
         self._memory = sf_runner_memory()
         self._lent = None
-        self._spare = None
-        self._work_host = None
-        self._work_dev = None
-        self._uploaded = None
+        self._spare = None      # (pinned, device) int32 room for captured calls' lists
+        self._captured = []     # their lists (pinned, device), which graphs read
         self.last_info = None
 
     def _create(self):
@@ -484,7 +482,7 @@ class ExtendAttention:
         slots = 31 if need <= 1 << 14 else 7 if need <= 1 << 18 else 4
         slot = max(int(m.pinned_bytes) // m.slots if m.slots else 0, (need + need // 4 + 1023) // 32 * 32)
         device = (max(int(m.device_bytes), int(m.need_device) * 5 // 4 + 4096) + 255) // 256 * 256
-        # One slot more, on both sides, for a captured call: sf_extend_attn's
+        # One slot more, on both sides, for captured calls: sf_extend_attn's
         # list has at most a row for each of the runner's.
         pinned = torch.empty((slots + 1) * slot, dtype=torch.uint8, pin_memory=True)
         work = torch.empty(device + slot, dtype=torch.uint8, device=self.device)
@@ -527,28 +525,39 @@ class ExtendAttention:
             info = self._call_captured(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream)
         else:
             _check("sf_runner_extend", st)
+            if self._spare is not None and self._spare[0].numel() * 4 < info.work_bytes:   # captured calls took it
+                self._spare = self._room(info.work_bytes // 4)
         self.last_info = info
         return out
 
+    def _room(self, ints):
+        return (torch.empty(ints, dtype=torch.int32, pin_memory=True),
+                torch.empty(ints, dtype=torch.int32, device=self.device))
+
+    def _captured_list(self, work):
+        """(pinned, device) lists with the rows of `work`, of this object's captured calls alone."""
+        for host, dev in self._captured:
+            if host.numel() == work.size and np.array_equal(host.numpy(), work):
+                return host, dev
+        if self._spare is not None and self._spare[0].numel() >= work.size:
+            host, dev = (t[:work.size] for t in self._spare)
+            self._spare = tuple(t[work.size:] for t in self._spare)
+        else:
+            try:
+                host, dev = self._room(work.size)
+            except RuntimeError as e:
+                raise RuntimeError("no room for a captured extend call's work list: make an eager call with this batch "
+                                   "before the capture") from e
+        host.numpy()[:] = work
+        self._captured.append((host, dev))
+        return host, dev
+
     def _call_captured(self, desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream):
-        info = sf_extend_info()
-        _check("sf_extend_attn_plan", lib().sf_extend_attn_plan(ctypes.byref(desc), lens.ctypes.data,
-                                                                qls.ctypes.data, None, 0, ctypes.byref(info)))
-        need = max(8, int(info.work_bytes) // 4)
-        if self._uploaded is not None:
-            self._uploaded.synchronize()
-        if self._work_host is None or self._work_host.numel() < need:
-            if self._spare is not None and self._spare[0].numel() >= need:
-                self._work_host, self._work_dev = self._spare   # kept as long as this object, as a graph reads them
-            else:
-                self._work_host = torch.empty(need, dtype=torch.int32, pin_memory=True)
-                self._work_dev = torch.empty(need, dtype=torch.int32, device=self.device)
-        info, _ = sf_extend_attn_plan(desc, lens, qls, work_host=self._work_host)
-        sf_extend_attn(desc, info, self._work_host, self._work_dev, q, k_pool, v_pool, block_table, out, lse,
-                       k_new=k_new, v_new=v_new, stream=stream)
-        ev = torch.cuda.Event()
-        ev.record(stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.current_stream())
-        self._uploaded = ev
+        info, work = sf_extend_attn_plan(desc, lens, qls)
+        if info.num_items > 0:
+            host, dev = self._captured_list(work[: info.work_bytes // 4])
+            sf_extend_attn(desc, info, host, dev, q, k_pool, v_pool, block_table, out, lse, k_new=k_new, v_new=v_new,
+                           stream=stream)
         return info
 
     def __del__(self):

@@ -5,6 +5,7 @@ import ctypes
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2601_12784_amd import binding as B
 
@@ -88,3 +89,20 @@ def test_runner_extend_rejects_missing_arguments():
     assert B.lib().sf_runner_extend(None, ctypes.byref(desc), lens.ctypes.data, lens.ctypes.data, None, None, None, None,
                                     None, None, None, None, ctypes.byref(B.sf_runner_memory()), None,
                                     ctypes.byref(B.sf_extend_info())) == 1
+
+
+def test_captured_calls_keep_their_lists():
+    """A captured call's list is its own: equal lists are shared, others take
+    further room, and without room the error says what to do."""
+    call = B.ExtendAttention(4, 1, 64)
+    call._spare = (torch.zeros(40, dtype=torch.int32), torch.zeros(40, dtype=torch.int32))
+    a, b = np.arange(16, dtype=np.int32), np.arange(24, dtype=np.int32)
+    ha, da = call._captured_list(a)
+    hb, db = call._captured_list(b)
+    assert np.array_equal(ha.numpy(), a) and np.array_equal(hb.numpy(), b) and da.numel() == 16 and db.numel() == 24
+    assert da.data_ptr() + 64 == db.data_ptr()
+    assert call._captured_list(a.copy())[0] is ha and call._spare[0].numel() == 0
+    call._room = lambda ints: (_ for _ in ()).throw(RuntimeError("capturing"))
+    with pytest.raises(RuntimeError, match="eager call"):
+        call._captured_list(np.zeros(8, np.int32))
+    assert np.array_equal(ha.numpy(), a) and len(call._captured) == 2

@@ -215,3 +215,42 @@ def test_streams_that_end_between_calls():
             assert torch.equal(out, want[which]), f"stream {i}"
     assert torch.equal(call(*args[0]), want[0])
     torch.cuda.synchronize()
+
+
+def test_graphs_of_one_object_keep_their_own_lists():
+    """Two graphs of different batches captured from one object, with a growing
+    eager call between the captures and eager calls between the replays: each
+    replay reads the work list of its own capture. A batch captured again shares
+    its list."""
+    ebs = [build_extend(lens, qls, 28, 4, 128, seed=50 + i) for i, (lens, qls) in enumerate(
+        [([300, 90], [300, 20]), ([2000, 40, 700], [64, 40, 700]), ([9000], [900])])]
+    args, want = [], []
+    for eb in ebs:
+        b = eb.batch
+        args.append((eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens,
+                     eb.q_lens, b.scale))
+        desc = B.make_desc(b.num_seqs, 28, 4, 128, b.block_table.shape[1], b.num_pages, b.scale)
+        info, work = B.sf_extend_attn_plan(desc, b.seq_lens, eb.q_lens)
+        want.append(torch.zeros((eb.num_rows, 28, 128), dtype=torch.float32, device="cuda"))
+        B.sf_extend_attn(desc, info, None, torch.from_numpy(work).cuda(), *args[-1][:4], want[-1])
+    outs = [torch.zeros_like(w) for w in want[:2]]
+    call = B.ExtendAttention(28, 4, 128)
+    graphs = []
+    for i in range(2):
+        call(*args[i])
+        torch.cuda.synchronize()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[i]):
+            call(*args[i], out=outs[i])
+            call(*args[i], out=outs[i])
+        call(*args[2])   # outgrows the lent memory
+        torch.cuda.synchronize()
+    assert len(call._captured) == 2
+    for r in range(4):
+        i = r % 2
+        for o in outs:
+            o.zero_()
+        graphs[i].replay()
+        call(*args[2 - r % 3])
+        torch.cuda.synchronize()
+        assert torch.equal(outs[i], want[i]) and not outs[1 - i].any(), f"replay {r}"
