@@ -104,6 +104,10 @@ namespace {
 
 constexpr int32_t kStepKeys = 2 * kPage;
 
+// Lengths go up to INT32_MAX, so rounding one up takes 64 bits.
+int32_t steps_of(int32_t keys) { return int32_t((int64_t(keys) + kStepKeys - 1) / kStepKeys); }
+int32_t pages_of(int32_t tokens) { return int32_t((int64_t(tokens) + kPage - 1) / kPage); }
+
 // Calls f(sequence, first new token, tokens, steps) for every block of at
 // most `per` new tokens (each is one item per KV head).
 template <class F>
@@ -111,7 +115,7 @@ void for_blocks(const sf_attn_desc* desc, const int32_t* lens, const int32_t* ne
   for (int32_t s = 0; s < desc->num_seqs; ++s)
     for (int32_t t0 = 0; t0 < new_lens[s]; t0 += per) {
       const int32_t nt = std::min(per, new_lens[s] - t0);
-      f(s, t0, nt, (lens[s] - new_lens[s] + t0 + nt + kStepKeys - 1) / kStepKeys);
+      f(s, t0, nt, steps_of(lens[s] - new_lens[s] + t0 + nt));
     }
 }
 
@@ -299,16 +303,16 @@ sf_status sf::extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_len
       merges += hkv;
       slots += int64_t(k) * hkv;
     }
-    longest = std::max<int64_t>(longest, (steps + k - 1) / k);
+    longest = std::max<int64_t>(longest, (int64_t(steps) + k - 1) / k);
   });
   int64_t stores = 0, store_pages = 0;
   if (store)
     for (int32_t s = 0; s < desc->num_seqs; ++s)
-      if (news[s] > 0) store_pages += (lens[s] + kPage - 1) / kPage - (lens[s] - news[s]) / kPage;
+      if (news[s] > 0) store_pages += pages_of(lens[s]) - (lens[s] - news[s]) / kPage;
   const int32_t run = store_pages > 2048 ? 4 : 1;
   if (store)
     for (int32_t s = 0; s < desc->num_seqs; ++s)
-      if (news[s] > 0) stores += ((lens[s] + kPage - 1) / kPage - (lens[s] - news[s]) / kPage + run - 1) / run;
+      if (news[s] > 0) stores += (pages_of(lens[s]) - (lens[s] - news[s]) / kPage + run - 1) / run;
   if (parts + merges + stores > INT32_MAX / kItemInts) return SF_ERR_INVALID_ARG;
   plan->rows = rows;
   plan->num_parts = int32_t(parts);
@@ -350,7 +354,7 @@ sf_status sf::extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_len
     int32_t* r = merge_rows + merges * kItemInts;
     int32_t qrow0 = 0;
     for (int32_t s = 0; s < desc->num_seqs; qrow0 += news[s++]) {
-      const int32_t first = lens[s] - news[s], end_page = (lens[s] + kPage - 1) / kPage;
+      const int32_t first = lens[s] - news[s], end_page = pages_of(lens[s]);
       for (int32_t p = first / kPage; news[s] > 0 && p < end_page; p += run, r += kItemInts) {
         const int32_t r8[kItemInts] = {s, p, std::min(run, end_page - p), first, lens[s], qrow0, 0, 0};
         std::memcpy(r, r8, sizeof r8);

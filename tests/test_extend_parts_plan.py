@@ -73,6 +73,22 @@ def test_plan_covers_every_step_once(case, cus):
     assert plan(lens, qls, hq, hkv, d, cus, False)[4].size == 0
 
 
+@pytest.mark.parametrize("length", [2**31 - 1, 2**31 - 20, 2**31 - 33])
+def test_longest_lengths(length):
+    """Lengths whose rounding up to a step or a page passes 31 bits."""
+    L, lens, qls, counts = B.lib(), np.array([length], np.int32), np.array([5], np.int32), np.zeros(5, np.int32)
+    desc = B.make_desc(1, 4, 1, 64, 1 << 27, 8, 0.1)
+    args = (ctypes.byref(desc), lens.ctypes.data, qls.ctypes.data, 256, 1)
+    assert L.sf_debug_extend_plan(*args, None, 0, counts.ctypes.data) == 3
+    work = np.zeros((int(counts[1:4].sum()), 8), np.int32)
+    assert L.sf_debug_extend_plan(*args, work.ctypes.data, work.nbytes, counts.ctypes.data) == 0
+    parts, store = work[: counts[1]], work[counts[1] + counts[2]:]
+    order = np.argsort(parts[:, 2])
+    assert parts[order[0], 2] == 0 and parts[order[-1], 6] == -(-length // 32)
+    assert np.array_equal(parts[order[:-1], 6], parts[order[1:], 2]) and np.all(parts[:, 6] > parts[:, 2])
+    assert store[:, 1].min() == (length - 5) // 16 and store[:, 1].max() + 1 == -(-length // 16)
+
+
 def test_plan_rejects_what_the_plain_plan_rejects():
     L = B.lib()
     counts = np.zeros(5, np.int32)
