@@ -438,7 +438,10 @@ sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info, c
  * destroyed or a call passes other memory (which first waits for the calls so
  * far). If a slot or the device memory is too small the call launches
  * nothing, writes the bytes it needs to need_slot and need_device and returns
- * SF_ERR_CAPACITY. Calls on one runner must not overlap on the host; a call on
+ * SF_ERR_CAPACITY. Walks are cut only into about 4 parts of 384 rows or 8 of
+ * 128 per compute unit, so need_device stays below 1 MB per compute unit at
+ * head_dim 128 (256 MB for 256), half that at 64; sf_extend_attn needs none of
+ * it. Calls on one runner must not overlap on the host; a call on
  * another stream than the runner's last extend call waits for its calls so far.
  * Nothing is recorded on a stream after the call it was given to, so it may be
  * destroyed between calls. Asynchronous on stream. Other errors as sf_extend_attn_plan and

@@ -448,12 +448,15 @@ class ExtendAttention:
     pinned memory that the launches read in place, so calls queue up behind
     each other without waiting. The pinned slots and the device memory for
     partial results are torch tensors that this object keeps and lends to the
-    runner. A stream that is being captured into a graph takes sf_extend_attn
-    instead, on a work list that the graph uploads at each replay. Captured
-    calls share a list only where it is the same; none is rewritten or freed
-    while the object lives, so the object must outlive the graphs. Pinned memory
-    can't be allocated during a capture, so an eager call keeps room for its own
-    batch's list: one that is captured after it allocates nothing."""
+    runner; where the device has no room for a cut plan's partial results, the
+    call takes sf_extend_attn, whose plan needs only its own list.
+
+    A stream that is being captured into a graph takes sf_extend_attn too, on a
+    work list that the graph uploads at each replay. Captured calls share a list
+    only where it is the same; none is rewritten or freed while the object lives,
+    so the object must outlive the graphs. Pinned memory can't be allocated
+    during a capture, so an eager call keeps room for its own batch's list: one
+    that is captured after it allocates nothing."""
 
     def __init__(self, num_q_heads, num_kv_heads, head_dim, device=None):
         self.hq, self.hkv, self.d = int(num_q_heads), int(num_kv_heads), int(head_dim)
@@ -518,7 +521,12 @@ class ExtendAttention:
                 ctypes.byref(self._memory), _stream(stream), ctypes.byref(info))
         st = self._L.sf_runner_extend(*args)
         if st == CAPACITY:
-            lent = self._lend(stream)
+            try:
+                lent = self._lend(stream)
+            except torch.OutOfMemoryError:
+                self.last_info = self._call_whole(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new,
+                                                  stream)
+                return out
             st = self._L.sf_runner_extend(*args)
             self._lent = lent
         if st == UNSUPPORTED:
@@ -558,6 +566,15 @@ class ExtendAttention:
             host, dev = self._captured_list(work[: info.work_bytes // 4])
             sf_extend_attn(desc, info, host, dev, q, k_pool, v_pool, block_table, out, lse, k_new=k_new, v_new=v_new,
                            stream=stream)
+        return info
+
+    def _call_whole(self, desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream):
+        info, work = sf_extend_attn_plan(desc, lens, qls)
+        dev = torch.from_numpy(work).to(self.device)   # uploaded when this returns
+        sf_extend_attn(desc, info, None, dev, q, k_pool, v_pool, block_table, out, lse, k_new=k_new, v_new=v_new,
+                       stream=stream)
+        if stream is not None:   # the list belongs to the current stream
+            torch.cuda.ExternalStream(_stream(stream), device=self.device).synchronize()
         return info
 
     def __del__(self):

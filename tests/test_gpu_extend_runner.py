@@ -254,3 +254,34 @@ def test_graphs_of_one_object_keep_their_own_lists():
         call(*args[2 - r % 3])
         torch.cuda.synchronize()
         assert torch.equal(outs[i], want[i]) and not outs[1 - i].any(), f"replay {r}"
+
+
+@pytest.mark.parametrize("side", [False, True])
+def test_no_device_memory_for_a_cut_plan(side):
+    """Where torch may not reserve the partial results of a cut plan, the call
+    takes the whole items' plan; a later call with memory cuts again."""
+    eb = build_extend([8000] * 4, [256] * 4, 28, 4, 128, seed=12)
+    b = eb.batch
+    args = (eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens, eb.q_lens,
+            b.scale)
+    desc = B.make_desc(4, 28, 4, 128, b.block_table.shape[1], b.num_pages, b.scale)
+    info, work = B.sf_extend_attn_plan(desc, b.seq_lens, eb.q_lens)
+    whole, out = (torch.zeros((eb.num_rows, 28, 128), dtype=torch.float32, device="cuda") for _ in range(2))
+    B.sf_extend_attn(desc, info, None, torch.from_numpy(work).cuda(), *args[:4], whole)
+    stream = torch.cuda.Stream() if side else None
+    call = B.ExtendAttention(28, 4, 128)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    room = torch.cuda.memory_reserved() + (8 << 20)   # the plan asks for about 50 MB
+    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        call(*args, out=out, stream=stream)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(out, whole) and call.last_info.num_items == info.num_items
+    out.zero_()
+    torch.cuda.synchronize()
+    call(*args, out=out, stream=stream)
+    torch.cuda.synchronize()
+    assert float((out - whole).norm() / whole.norm()) < 2.0 ** -17 and not torch.equal(out, whole)
