@@ -436,27 +436,32 @@ sf_status sf_extend_attn(const sf_attn_desc* desc, const sf_extend_info* info, c
  * aligned, `slots` <= 32 equal slots of whole 32-byte rows, one plan each) and
  * device memory, both the caller's and unchanged until the runner is
  * destroyed or a call passes other memory (which first waits for the calls so
- * far). If a slot or the device memory is too small the call launches
- * nothing, writes the bytes it needs to need_slot and need_device and returns
- * SF_ERR_CAPACITY. Walks are cut only into about 4 parts of 384 rows or 8 of
- * 128 per compute unit, so need_device stays below 1 MB per compute unit at
- * head_dim 128 (256 MB for 256), half that at 64; sf_extend_attn needs none of
- * it. Calls on one runner must not overlap on the host; a call on
- * another stream than the runner's last extend call waits for its calls so far.
- * Nothing is recorded on a stream after the call it was given to, so it may be
- * destroyed between calls. Asynchronous on stream. Other errors as sf_extend_attn_plan and
- * sf_extend_attn; SF_ERR_UNSUPPORTED, with nothing launched, also on a stream
- * that is being captured into a graph.
+ * far). With device_per_call = 1 the device memory is this call's alone: the
+ * caller keeps it until the call's launches have ended (in stream order is
+ * enough), and nothing is waited for when it changes. The call
+ * writes the bytes that its plan takes to need_slot and need_device; if a slot
+ * or the device memory is too small it launches nothing and returns
+ * SF_ERR_CAPACITY. Walks are cut only
+ * into about 4 parts of 384 rows or 8 of 128 per compute unit, so need_device
+ * stays below 1 MB per compute unit at head_dim 128 (256 MB for 256), half
+ * that at 64; sf_extend_attn needs none of it.
+ *
+ * Calls on one runner must not overlap on the host; a call on another stream
+ * than the runner's last extend call waits for its calls so far. Nothing is
+ * recorded on a stream after the call it was given to, so it may be destroyed
+ * between calls. Asynchronous on stream. Other errors as sf_extend_attn_plan
+ * and sf_extend_attn; SF_ERR_UNSUPPORTED, with nothing launched, also on a
+ * stream that is being captured into a graph.
  */
 typedef struct sf_runner_memory {
   void* pinned;
   uint64_t pinned_bytes;
   void* device;
   uint64_t device_bytes;
-  uint64_t need_slot;        /* out, with SF_ERR_CAPACITY */
+  uint64_t need_slot;        /* out, with SF_OK and SF_ERR_CAPACITY */
   uint64_t need_device;
   int32_t slots;
-  int32_t reserved;
+  int32_t device_per_call;   /* 1: as described above; else 0 */
 } sf_runner_memory;
 
 sf_status sf_runner_extend(sf_runner* runner, const sf_attn_desc* desc, const int32_t* seq_lens_host,

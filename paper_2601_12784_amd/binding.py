@@ -7,9 +7,11 @@ there is no fallback path.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import re
+import threading
 
 import numpy as np
 import torch
@@ -69,7 +71,7 @@ class sf_runner_extras(ctypes.Structure):
 class sf_runner_memory(ctypes.Structure):
     _fields_ = [("pinned", ctypes.c_void_p), ("pinned_bytes", ctypes.c_uint64), ("device", ctypes.c_void_p),
                 ("device_bytes", ctypes.c_uint64), ("need_slot", ctypes.c_uint64), ("need_device", ctypes.c_uint64),
-                ("slots", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+                ("slots", ctypes.c_int32), ("device_per_call", ctypes.c_int32)]
 
 
 class sf_cost_model(ctypes.Structure):
@@ -441,15 +443,78 @@ def sf_extend_attn(desc, info, work_host, work_dev, q, k_pool, v_pool, block_tab
         _stream(stream)))
 
 
+_cus = {}
+
+
+def _compute_units(index):
+    if index not in _cus:
+        _cus[index] = torch.cuda.get_device_properties(index).multi_processor_count
+    return _cus[index]
+
+
+class _SharedScratch:
+    """Device memory for the partial results of cut plans, shared by the live
+    ExtendAttention objects: one block per thread and stream. A thread's calls on
+    one stream run one after the other, so each may overwrite what the last one
+    left, and torch's allocator takes a dropped block back in that stream's order.
+    At most BLOCKS blocks are kept (the least recently used goes first), none
+    once the last object is gone. Per-object memory would cost every new object
+    of a process a device allocation (30 to 80 us) while others live."""
+    BLOCKS = 4
+
+    def __init__(self):
+        self._lock = threading.Lock()
+        self._blocks = {}   # (thread, device, stream) -> tensor, least recently used first
+        self._live = 0
+
+    def join(self):
+        with self._lock:
+            self._live += 1
+
+    def leave(self):
+        with self._lock:
+            self._live -= 1
+            if self._live == 0:
+                self._blocks.clear()
+
+    def get(self, device, stream):
+        """The block of this thread and stream (the current one's handle), or None."""
+        key = (threading.get_ident(), device, stream)
+        with self._lock:
+            block = self._blocks.pop(key, None)
+            if block is not None:
+                self._blocks[key] = block
+            return block
+
+    def grow(self, device, stream, nbytes):
+        """Sees to a block of at least nbytes."""
+        key = (threading.get_ident(), device, stream)
+        with self._lock:
+            block = self._blocks.pop(key, None)
+            if block is not None and block.numel() >= nbytes:
+                self._blocks[key] = block
+                return
+            block = None   # back to the allocator before the larger one is taken
+            self._blocks[key] = torch.empty(nbytes, dtype=torch.uint8, device=device)
+            while len(self._blocks) > self.BLOCKS:
+                del self._blocks[next(iter(self._blocks))]
+
+
+_scratch = _SharedScratch()
+
+
 class ExtendAttention:
     """Plans and launches extend attention for one batch of re-prefills.
 
     Each call goes through a native runner (sf_runner_extend): it plans into
     pinned memory that the launches read in place, so calls queue up behind
     each other without waiting. The pinned slots and the device memory for
-    partial results are torch tensors that this object keeps and lends to the
-    runner; where the device has no room for a cut plan's partial results, the
-    call takes sf_extend_attn, whose plan needs only its own list.
+    partial results are torch tensors that are lent to the runner: this object
+    keeps the slots and up to 1 MiB of device memory, larger partial results (up
+    to 256 MB) go to a block that all live objects share. (A call with a `stream`
+    argument keeps what it needs, as the block belongs to the current stream.)
+    Where the device has no room for a cut plan's partial results, the call takes
+    sf_extend_attn, whose plan needs only its own list.
 
     A stream that is being captured into a graph takes sf_extend_attn too, on a
     work list that the graph uploads at each replay. Captured calls share a list
@@ -464,37 +529,83 @@ class ExtendAttention:
         self._L = None
         self._runner = ctypes.c_void_p()
         self._memory = sf_runner_memory()
-        self._lent = None
-        self._spare = None      # (pinned, device) int32 room for captured calls' lists
+        self._lent = []         # what _memory lends for longer than a call; before it, what calls may still use
+        self._large = True      # the last plan took the shared block; a new object looks for one
+        self._spare = [None, 0, None, 0, 0]   # pinned, device (offsets in bytes) and the bytes left for captured lists
         self._captured = []     # their lists (pinned, device), which graphs read
         self.last_info = None
 
-    def _create(self):
-        self._L = lib()
-        shape = make_desc(0, self.hq, self.hkv, self.d, 1, 0, 1.0)
-        with torch.cuda.device(self.device):
-            opts = make_opts(num_cus=torch.cuda.get_device_properties(self.device).multi_processor_count)
-            _check("sf_runner_create", self._L.sf_runner_create(ctypes.byref(shape), ctypes.byref(opts),
-                                                                ctypes.byref(self._runner)))
+    # What a new object lends: slots and device memory that hold most short
+    # plans, so that its first call seldom has to ask and plan twice. First
+    # calls, from call to result, 28/4 heads (us; in brackets with the plan of
+    # whole items alone, in braces when every first call asked): 1000 tokens
+    # 76 [95] {83}, 60 tokens 50 [58] {52}; with all earlier objects alive, whose
+    # pinned memory torch cannot hand on, 145 [137] {190} and 100 [108] {96}.
+    SLOTS, SLOT, DEVICE = 15, 1 << 15, 1 << 16
+    KEEP = 1 << 20   # device bytes of a plan beyond which it takes the shared block
 
-    def _lend(self, stream):
-        """Larger memory for the runner, as its last call asked. What it held
-        stays alive until the next call has waited for the steps that use it."""
+    def _create(self):
+        if self._L is None:
+            L = lib()
+            shape = make_desc(0, self.hq, self.hkv, self.d, 1, 0, 1.0)
+            with contextlib.nullcontext() if self._ordered(None) else torch.cuda.device(self.device):
+                opts = make_opts(num_cus=_compute_units(torch.cuda.current_device()))
+                _check("sf_runner_create", L.sf_runner_create(ctypes.byref(shape), ctypes.byref(opts),
+                                                              ctypes.byref(self._runner)))
+            self._L, self._scratch = L, _scratch
+            _scratch.join()
+        self._lend(self.SLOT, self.DEVICE - self.SLOT, None)
+
+    def _lend(self, slot, device, stream):
+        """Other memory for the runner. What it held stays alive until a call has
+        waited for the calls that use it."""
         m = self._memory
-        need = int(m.need_slot)
-        slots = 31 if need <= 1 << 14 else 7 if need <= 1 << 18 else 4
-        slot = max(int(m.pinned_bytes) // m.slots if m.slots else 0, (need + need // 4 + 1023) // 32 * 32)
-        device = (max(int(m.device_bytes), int(m.need_device) * 5 // 4 + 4096) + 255) // 256 * 256
+        slots = self.SLOTS if slot <= 1 << 16 else 4
         # One slot more, on both sides, for captured calls: sf_extend_attn's
         # list has at most a row for each of the runner's.
         pinned = torch.empty((slots + 1) * slot, dtype=torch.uint8, pin_memory=True)
         work = torch.empty(device + slot, dtype=torch.uint8, device=self.device)
-        self._spare = (pinned[slots * slot:].view(torch.int32), work[device:].view(torch.int32))
+        self._spare = [pinned, slots * slot, work, device, slot]
         if stream is not None:   # the allocation is ordered on the current stream
             torch.cuda.current_stream(self.device).synchronize()
         m.pinned, m.pinned_bytes, m.slots = pinned.data_ptr(), slots * slot, slots
         m.device, m.device_bytes = work.data_ptr(), device
-        return pinned, work
+        self._lent.append((pinned, work))
+
+    def _ordered(self, stream):
+        """Whether the call's launches go to the stream that torch's allocator serves now."""
+        return stream is None and (self.device.index is None or self.device.index == torch.cuda.current_device())
+
+    def _grow(self, stream):
+        """More memory, as the last call asked."""
+        m = self._memory
+        need = (int(m.need_device) * 5 // 4 + 4096 + 255) // 256 * 256
+        slot, device = int(m.pinned_bytes) // m.slots, int(m.device_bytes)
+        self._large = need > self.KEEP and self._ordered(stream)
+        if self._large:
+            self._scratch.grow(self.device, _stream(None), need)
+        else:
+            device = max(device, need)
+        if m.need_slot > slot:
+            slot = (int(m.need_slot) * 5 // 4 + 1023) // 256 * 256
+        if slot != int(m.pinned_bytes) // m.slots or device != m.device_bytes:
+            self._lend(slot, device, stream)
+
+    def _run(self, args, stream):
+        """One sf_runner_extend, on the shared block where the last plan took more than is kept."""
+        m = self._memory
+        block = self._scratch.get(self.device, args[13]) if self._large and self._ordered(stream) else None
+        if block is None:
+            st = self._L.sf_runner_extend(*args)
+            if len(self._lent) > 1 and st in (0, CAPACITY):   # calls on what was lent before have been waited for
+                del self._lent[:-1]
+            return st
+        kept = m.device, m.device_bytes
+        m.device, m.device_bytes, m.device_per_call = block.data_ptr(), block.numel(), 1
+        st = self._L.sf_runner_extend(*args)
+        m.device, m.device_bytes, m.device_per_call = *kept, 0
+        self._large = m.need_device > m.device_bytes
+        return st
 
     def __call__(self, q, k_pool, v_pool, block_table, seq_lens, q_lens, scale, out=None, lse=None,
                  k_new=None, v_new=None, stream=None):
@@ -509,70 +620,67 @@ class ExtendAttention:
         if out is None:
             out = torch.empty((rows, self.hq, self.d), dtype=torch.float32, device=self.device)
         _check_extend(desc, rows, q, k_pool, v_pool, block_table, out, lse, k_new, v_new)
-        if self._L is None:
-            if torch.cuda.is_current_stream_capturing():   # a runner's events are not created in a capture
-                self.last_info = self._call_captured(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new,
-                                                     v_new, stream)
-                return out
-            self._create()
         info = sf_extend_info()
-        args = (self._runner, ctypes.byref(desc), _host_addr(lens), _host_addr(qls), q.data_ptr(), _addr(k_new),
-                _addr(v_new), k_pool.data_ptr(), v_pool.data_ptr(), block_table.data_ptr(), out.data_ptr(), _addr(lse),
-                ctypes.byref(self._memory), _stream(stream), ctypes.byref(info))
-        st = self._L.sf_runner_extend(*args)
+        tensors = (q, k_pool, v_pool, block_table, out, lse, k_new, v_new)
+        try:
+            if not self._lent:
+                if torch.cuda.is_current_stream_capturing():   # nothing is created in a capture
+                    self.last_info = self._call_captured(desc, lens, qls, tensors, stream)
+                    return out
+                self._create()
+            args = (self._runner, ctypes.byref(desc), _host_addr(lens), _host_addr(qls), q.data_ptr(), _addr(k_new),
+                    _addr(v_new), k_pool.data_ptr(), v_pool.data_ptr(), block_table.data_ptr(), out.data_ptr(), _addr(lse),
+                    ctypes.byref(self._memory), _stream(stream), ctypes.byref(info))
+            st = self._run(args, stream)
+            if st == CAPACITY:
+                self._grow(stream)
+                st = self._run(args, stream)
+        except torch.OutOfMemoryError:
+            st = CAPACITY
         if st == CAPACITY:
-            try:
-                lent = self._lend(stream)
-            except torch.OutOfMemoryError:
-                self.last_info = self._call_whole(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new,
-                                                  stream)
-                return out
-            st = self._L.sf_runner_extend(*args)
-            self._lent = lent
+            self.last_info = self._call_whole(desc, lens, qls, tensors, stream)
+            return out
         if st == UNSUPPORTED:
-            info = self._call_captured(desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream)
+            info = self._call_captured(desc, lens, qls, tensors, stream)
         else:
             _check("sf_runner_extend", st)
-            if self._spare is not None and self._spare[0].numel() * 4 < info.work_bytes:   # captured calls took it
-                self._spare = self._room(info.work_bytes // 4)
+            if self._spare[4] < info.work_bytes:   # captured calls took it
+                self._spare = self._room(info.work_bytes)
         self.last_info = info
         return out
 
-    def _room(self, ints):
-        return (torch.empty(ints, dtype=torch.int32, pin_memory=True),
-                torch.empty(ints, dtype=torch.int32, device=self.device))
+    def _room(self, nbytes):
+        return [torch.empty(nbytes, dtype=torch.uint8, pin_memory=True), 0,
+                torch.empty(nbytes, dtype=torch.uint8, device=self.device), 0, nbytes]
 
     def _captured_list(self, work):
         """(pinned, device) lists with the rows of `work`, of this object's captured calls alone."""
         for host, dev in self._captured:
             if host.numel() == work.size and np.array_equal(host.numpy(), work):
                 return host, dev
-        if self._spare is not None and self._spare[0].numel() >= work.size:
-            host, dev = (t[:work.size] for t in self._spare)
-            self._spare = tuple(t[work.size:] for t in self._spare)
-        else:
+        if self._spare[4] < work.nbytes:
             try:
-                host, dev = self._room(work.size)
+                self._spare = self._room(work.nbytes)
             except RuntimeError as e:
                 raise RuntimeError("no room for a captured extend call's work list: make an eager call with this batch "
                                    "before the capture") from e
+        pinned, p, device, d, left = self._spare
+        host, dev = (t[at: at + work.nbytes].view(torch.int32) for t, at in ((pinned, p), (device, d)))
+        self._spare = [pinned, p + work.nbytes, device, d + work.nbytes, left - work.nbytes]
         host.numpy()[:] = work
         self._captured.append((host, dev))
         return host, dev
 
-    def _call_captured(self, desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream):
+    def _call_captured(self, desc, lens, qls, tensors, stream):
         info, work = sf_extend_attn_plan(desc, lens, qls)
         if info.num_items > 0:
-            host, dev = self._captured_list(work[: info.work_bytes // 4])
-            sf_extend_attn(desc, info, host, dev, q, k_pool, v_pool, block_table, out, lse, k_new=k_new, v_new=v_new,
-                           stream=stream)
+            sf_extend_attn(desc, info, *self._captured_list(work[: info.work_bytes // 4]), *tensors, stream=stream)
         return info
 
-    def _call_whole(self, desc, lens, qls, q, k_pool, v_pool, block_table, out, lse, k_new, v_new, stream):
+    def _call_whole(self, desc, lens, qls, tensors, stream):
         info, work = sf_extend_attn_plan(desc, lens, qls)
         dev = torch.from_numpy(work).to(self.device)   # uploaded when this returns
-        sf_extend_attn(desc, info, None, dev, q, k_pool, v_pool, block_table, out, lse, k_new=k_new, v_new=v_new,
-                       stream=stream)
+        sf_extend_attn(desc, info, None, dev, *tensors, stream=stream)
         if stream is not None:   # the list belongs to the current stream
             torch.cuda.ExternalStream(_stream(stream), device=self.device).synchronize()
         return info
@@ -580,8 +688,9 @@ class ExtendAttention:
     def __del__(self):
         r = getattr(self, "_runner", None)
         if r is not None and r.value:
-            self._L.sf_runner_destroy(r)   # waits for the steps that use the lent memory
+            self._L.sf_runner_destroy(r)   # waits for the calls that use the lent memory
             r.value = None
+            self._scratch.leave()
 
 
 class PagePool:

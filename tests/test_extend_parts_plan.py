@@ -2,6 +2,7 @@
 new tokens in exactly one part, slots and merges that fit together, every page
 of new tokens stored once; and argument checks that need no device."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -111,14 +112,39 @@ def test_captured_calls_keep_their_lists():
     """A captured call's list is its own: equal lists are shared, others take
     further room, and without room the error says what to do."""
     call = B.ExtendAttention(4, 1, 64)
-    call._spare = (torch.zeros(40, dtype=torch.int32), torch.zeros(40, dtype=torch.int32))
+    call._spare = [torch.zeros(160, dtype=torch.uint8), 0, torch.zeros(192, dtype=torch.uint8), 32, 160]
     a, b = np.arange(16, dtype=np.int32), np.arange(24, dtype=np.int32)
     ha, da = call._captured_list(a)
     hb, db = call._captured_list(b)
     assert np.array_equal(ha.numpy(), a) and np.array_equal(hb.numpy(), b) and da.numel() == 16 and db.numel() == 24
     assert da.data_ptr() + 64 == db.data_ptr()
-    assert call._captured_list(a.copy())[0] is ha and call._spare[0].numel() == 0
-    call._room = lambda ints: (_ for _ in ()).throw(RuntimeError("capturing"))
+    assert call._captured_list(a.copy())[0] is ha and call._spare[4] == 0
+    call._room = lambda nbytes: (_ for _ in ()).throw(RuntimeError("capturing"))
     with pytest.raises(RuntimeError, match="eager call"):
         call._captured_list(np.zeros(8, np.int32))
     assert np.array_equal(ha.numpy(), a) and len(call._captured) == 2
+
+
+def test_shared_scratch_is_per_thread_and_stream_and_bounded():
+    pool = B._SharedScratch()
+    cpu = torch.device("cpu")
+    pool.join()
+    pool.join()
+    pool.grow(cpu, 1, 1000)
+    a = pool.get(cpu, 1)
+    pool.grow(cpu, 1, 900)
+    assert pool.get(cpu, 1) is a and pool.get(cpu, 2) is None
+    seen = []
+    t = threading.Thread(target=lambda: seen.append(pool.get(cpu, 1)))
+    t.start()
+    t.join()
+    assert seen == [None]
+    for stream in (2, 3, 4):
+        pool.grow(cpu, stream, 100)
+    assert pool.get(cpu, 1) is a          # used last: stream 2 goes first
+    pool.grow(cpu, 5, 100)
+    assert pool.get(cpu, 2) is None and pool.get(cpu, 1) is a and len(pool._blocks) == pool.BLOCKS
+    pool.leave()
+    assert pool.get(cpu, 1) is a
+    pool.leave()
+    assert not pool._blocks

@@ -3,6 +3,7 @@ one: key walks cut into parts, 128-row items, the page-wise store, and calls
 that queue up behind each other. Against the fp64 oracle at
 |gpu - ref| <= 2e-3 + 1e-2 |ref|; stores bit for bit."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -285,3 +286,53 @@ def test_no_device_memory_for_a_cut_plan(side):
     call(*args, out=out, stream=stream)
     torch.cuda.synchronize()
     assert float((out - whole).norm() / whole.norm()) < 2.0 ** -17 and not torch.equal(out, whole)
+
+
+def test_objects_share_scratch_over_threads_and_streams():
+    """Two objects per thread in three threads, two of them on one stream and one
+    on its own, all with cut plans at once: partial results are shared by the
+    objects of a thread and stream, and by nobody else."""
+    ebs = [build_extend(lens, qls, 28, 4, 128, seed=80 + i) for i, (lens, qls) in enumerate(
+        [([8000] * 4, [256] * 4), ([3000, 2900], [260, 200]), ([1000], [1000])])]
+    data, want = [], []
+    for eb in ebs:
+        b = eb.batch
+        data.append((eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens,
+                     eb.q_lens, b.scale))
+        want.append(B.ExtendAttention(28, 4, 128)(*data[-1]))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(n, stream):
+        with torch.cuda.stream(stream):
+            calls = [B.ExtendAttention(28, 4, 128) for _ in range(2)]
+            outs = [(i, calls[i % 2](*data[(n + i) % 3])) for i in range(24)]
+            stream.synchronize()
+            wrong.extend((n, i) for i, out in outs if not torch.equal(out, want[(n + i) % 3]))
+
+    shared = torch.cuda.Stream()
+    threads = [threading.Thread(target=work, args=(n, s)) for n, s in enumerate([shared, shared, torch.cuda.Stream()])]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong and not B._scratch._blocks
+
+
+@pytest.mark.parametrize("lens,earlier", [([60], False), ([1000], True)])
+def test_a_new_objects_first_call_plans_once(lens, earlier):
+    """A short call fits what a new object lends, and a longer one the block that
+    an object still alive has left."""
+    eb = build_extend(lens, lens, 28, 4, 128, seed=3)
+    b = eb.batch
+    args = (eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens, eb.q_lens,
+            b.scale)
+    alive = B.ExtendAttention(28, 4, 128)
+    if earlier:
+        want = alive(*args)
+    asked = []
+    call = B.ExtendAttention(28, 4, 128)
+    call._grow = lambda stream: asked.append(stream) or B.ExtendAttention._grow(call, stream)
+    out = call(*args)
+    torch.cuda.synchronize()
+    assert not asked and (not earlier or torch.equal(out, want))
