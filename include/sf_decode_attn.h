@@ -274,7 +274,8 @@ void sf_runner_destroy(sf_runner* runner);
  * work_bytes plus an appending step's extras for up to max_num_seqs
  * sequences; workspace_bytes and work_bytes as sf_runner_plan reports
  * them (work_host NULL) for the largest batch the caller will step, with the
- * runner's options. Growing the workspace synchronizes `stream` first (the
+ * runner's options. Steps of every kind over that batch or over fewer, shorter
+ * sequences then fit (with chunk_pages set: over that batch). Growing the workspace synchronizes `stream` first (the
  * old one may still be in use); a ring buffer grows after the step that last
  * read it has ended. A step whose plan needs more than the runner holds grows
  * it the same way inside sf_runner_step: a stall in that step, which a
@@ -595,6 +596,13 @@ double sf_cost_ideal_gain(const sf_cost_model* model, double length);
 sf_status sf_route(const sf_cost_model* model, double mu, int32_t min_initial_version,
                    sf_instance_state* inst, int32_t num_inst, const sf_trajectory* trajs,
                    int32_t num_trajs, int32_t* target, int32_t* num_routed);
+
+/*
+ * Test support: bytes[0] of device memory and bytes[1] per ring slot that
+ * sf_runner_reserve sees to for a runner of that shape and options; host only.
+ */
+sf_status sf_debug_runner_reserve(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
+                                  uint64_t work_bytes, int32_t max_num_seqs, uint64_t* bytes);
 
 /*
  * Test support: the plan sf_runner_extend makes for a device of num_cus

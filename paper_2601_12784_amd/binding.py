@@ -127,6 +127,7 @@ def lib():
     L.sf_extend_attn.argtypes = [P(sf_attn_desc), P(sf_extend_info), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.sf_runner_extend.argtypes = [vp, P(sf_attn_desc), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, P(sf_runner_memory),
                                    vp, P(sf_extend_info)]
+    L.sf_debug_runner_reserve.argtypes = [P(sf_attn_desc), P(sf_plan_opts), ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int32, vp]
     L.sf_debug_extend_plan.argtypes = [P(sf_attn_desc), vp, vp, ctypes.c_int32, ctypes.c_int32, vp, ctypes.c_uint64, vp]
     L.sf_runner_plan.argtypes = [P(sf_attn_desc), vp, P(sf_plan_opts), ctypes.c_int32, vp, ctypes.c_uint64,
                                  P(sf_plan_info)]
@@ -152,7 +153,8 @@ def lib():
                "sf_decode_attn_append", "sf_page_pool_create", "sf_page_pool_claim", "sf_page_pool_alloc",
                "sf_page_pool_release", "sf_page_table_step", "sf_route", "sf_extend_attn_plan",
                "sf_extend_attn", "sf_decode_attn_fp8", "sf_kv_quantize_fp8", "sf_runner_create",
-               "sf_runner_step", "sf_runner_extend", "sf_runner_plan", "sf_debug_extend_plan", "sf_debug_stream_read", "sf_decode_attn_scratch"):
+               "sf_runner_step", "sf_runner_extend", "sf_runner_plan", "sf_debug_extend_plan",
+               "sf_debug_runner_reserve", "sf_debug_stream_read", "sf_decode_attn_scratch"):
         getattr(L, fn).restype = ctypes.c_int
     L.sf_status_string.argtypes = [ctypes.c_int]
     L.sf_status_string.restype = ctypes.c_char_p
@@ -583,7 +585,7 @@ class ExtendAttention:
         slot, device = int(m.pinned_bytes) // m.slots, int(m.device_bytes)
         self._large = need > self.KEEP and self._ordered(stream)
         if self._large:
-            self._scratch.grow(self.device, _stream(None), need)
+            self._scratch.grow(torch.cuda.current_device(), _stream(None), need)
         else:
             device = max(device, need)
         if m.need_slot > slot:
@@ -594,7 +596,9 @@ class ExtendAttention:
     def _run(self, args, stream):
         """One sf_runner_extend, on the shared block where the last plan took more than is kept."""
         m = self._memory
-        block = self._scratch.get(self.device, args[13]) if self._large and self._ordered(stream) else None
+        block = None
+        if self._large and self._ordered(stream):
+            block = self._scratch.get(torch.cuda.current_device(), args[13])
         if block is None:
             st = self._L.sf_runner_extend(*args)
             if len(self._lent) > 1 and st in (0, CAPACITY):   # calls on what was lent before have been waited for

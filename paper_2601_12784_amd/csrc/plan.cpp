@@ -431,6 +431,10 @@ double runner_estimate(const RunnerCost& c, int64_t total, int64_t workers, int6
          (partials > 0 ? c.merge + kPartialUs * double(partials) + kDepthUs * double(std::max<int64_t>(0, depth - kDepth)) : 0.0);
 }
 
+bool slices_left_to_planner(const sf_plan_opts& o) {
+  return o.chunk_pages == 0 && o.workers_per_cu == 0 && o.min_chunk_pages == 0 && o.xcd_parity_skew == 0 && o.num_cus >= 0;
+}
+
 }  // namespace
 
 sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts,
@@ -438,9 +442,7 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   const bool fp8 = kind == StepKind::kFp8, append = kind == StepKind::kAppend;
   sf_plan_opts o = {};
   if (opts) o = *opts;
-  // The caller's own choice of slices stands.
-  const bool free_choice =
-      o.chunk_pages == 0 && o.workers_per_cu == 0 && o.min_chunk_pages == 0 && o.xcd_parity_skew == 0 && o.num_cus >= 0;
+  const bool free_choice = slices_left_to_planner(o);   // the caller's own choice of slices stands
   if (fp8 && o.workers_per_cu == 0) o.workers_per_cu = kFp8WorkersPerCu;
   auto slices = [&]() {
     return sf_decode_attn_plan(desc, seq_lens_host, &o, work_host, work_capacity_bytes, info);
@@ -578,13 +580,57 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   return SF_OK;
 }
 
-// Up to 4 workers per CU while the batch has no more pairs than that, 8 above
-// (or where a workgroup's waves share a segment: then half as many segments).
-sf::PairPlanMost sf::pair_plan_most(const sf_attn_desc* shape, const sf_plan_opts* opts, int32_t num_seqs) {
-  const int64_t cus = opts && opts->num_cus > 0 ? opts->num_cus : kDefaultNumCus;
+// A batch of at most num_seqs sequences, whatever its lengths and the kind of
+// its step, is planned as one of
+//   equal slices: at most W workers (the options' per CU; left to the planner,
+//     kDefaultWorkersPerCu, or kFp8WorkersPerCu over an fp8 cache). Each of the
+//     W - 1 boundaries between them adds a segment to a pair and may cut it;
+//   segments of pairs (options left to the planner): at most 8 workers per CU,
+//     and as many segments where the pairs alone are more than 4 per CU, half
+//     as many otherwise (or where a workgroup's waves share a segment).
+// A forced slice size has no such bound: the caller's bytes stand alone.
+sf::ReserveBytes sf::reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
+                                   uint64_t work_bytes, int32_t num_seqs) {
+  const sf_plan_opts none = {};
+  const sf_plan_opts& o = opts ? *opts : none;
+  const int64_t cus = o.num_cus > 0 ? o.num_cus : kDefaultNumCus;
   const int64_t pairs = int64_t(num_seqs) * shape->num_kv_heads;
-  const int64_t segments = pairs > 4 * cus ? 8 * cus : 4 * cus;
-  return {segments, 8 * cus + segments + std::min(pairs, segments / 2)};
+  const uint64_t pages = (uint64_t(num_seqs) * 4 + 31) / 32 * 32;   // an appending step's new pages, as kept
+  // an appending step also keeps a copy of at most one row per work item
+  int64_t partials = 0, rows = 0, append_rows = 0;
+  auto plan = [&](int64_t workers, int64_t segments, int64_t cut_segments, int64_t cut, bool appending) {
+    partials = std::max(partials, cut_segments);
+    rows = std::max(rows, workers + segments + cut);
+    if (appending) append_rows = std::max(append_rows, workers + 2 * segments + cut);
+  };
+  auto slices = [&](int64_t wpc, bool appending) {
+    const int64_t w = std::min<int64_t>(wpc * cus, INT32_MAX / 2), cut = std::min(pairs, w - 1);
+    plan(w, pairs + w - 1, w - 1 + cut, cut, appending);
+  };
+  if (o.chunk_pages == 0) {
+    slices(o.workers_per_cu ? o.workers_per_cu : kDefaultWorkersPerCu, true);
+    if (o.workers_per_cu == 0) slices(kFp8WorkersPerCu, false);
+    const int64_t segments = pairs > 4 * cus ? 8 * cus : 4 * cus;
+    if (slices_left_to_planner(o)) plan(8 * cus, segments, segments, std::min(pairs, segments / 2), true);
+  }
+  const uint64_t head_rows = uint64_t(partials) * (shape->num_q_heads / shape->num_kv_heads);
+  workspace_bytes = std::max(workspace_bytes, align256(head_rows * shape->head_dim * 4) + align256(head_rows * 4));
+  const uint64_t row_bytes = kItemInts * 4;
+  const uint64_t slot = std::max(2 * work_bytes, std::max(uint64_t(rows), uint64_t(append_rows)) * row_bytes) + pages;
+  // on the device: the partial results, then copies of the merge rows (at most
+  // the work list), and of an appending step's rows and new pages
+  return {align256(workspace_bytes) + std::max(work_bytes, uint64_t(std::max(rows, append_rows)) * row_bytes) + pages,
+          (slot + 4095) / 4096 * 4096};
+}
+
+extern "C" sf_status sf_debug_runner_reserve(const sf_attn_desc* shape, const sf_plan_opts* opts,
+                                             uint64_t workspace_bytes, uint64_t work_bytes, int32_t max_num_seqs,
+                                             uint64_t* bytes) {
+  if (!shape || !bytes || max_num_seqs < 0 || shape->num_kv_heads <= 0) return SF_ERR_INVALID_ARG;
+  const ReserveBytes b = reserve_bytes(shape, opts, workspace_bytes, work_bytes, max_num_seqs);
+  bytes[0] = b.device;
+  bytes[1] = b.slot;
+  return SF_OK;
 }
 
 extern "C" sf_status sf_runner_plan(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts,

@@ -493,24 +493,12 @@ extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, u
                                        int32_t max_num_seqs, void* stream) {
   if (!r || max_num_seqs < 0) return SF_ERR_INVALID_ARG;
   hipStream_t main = static_cast<hipStream_t>(stream);
-  // Smaller batches than the one reserved for may be planned as segments of
-  // pairs, which take other shares of the memory: up to most.partials, and up
-  // to most.rows (a batch with rows for a quarter of that or less has too few
-  // pages to come near it: four times its own rows then).
-  const sf::PairPlanMost most = sf::pair_plan_most(&r->shape, &r->opts, max_num_seqs);
-  const uint64_t head_rows = uint64_t(most.partials) * (r->shape.num_q_heads / r->shape.num_kv_heads);
-  workspace_bytes = std::max(workspace_bytes, sf::align256(head_rows * r->shape.head_dim * 4) + sf::align256(head_rows * 4));
-  work_bytes = std::max(work_bytes, std::min(uint64_t(most.rows) * sf::kItemInts * 4, 4 * work_bytes));
-  // partials, then the device copy of the merge rows (at most the work
-  // list's size) and new_pages
-  sf_status st = grow_device(r, &r->workspace, &r->workspace_bytes,
-                             sf::align256(workspace_bytes) + work_bytes + (uint64_t(max_num_seqs) * 4 + 31) / 32 * 32,
-                             main);
+  // A smaller batch, or a step of another kind, may be planned in another way
+  // than the batch reserved for and take more than it.
+  const sf::ReserveBytes need = sf::reserve_bytes(&r->shape, &r->opts, workspace_bytes, work_bytes, max_num_seqs);
+  sf_status st = grow_device(r, &r->workspace, &r->workspace_bytes, need.device, main);
   if (st != SF_OK) return st;
-  // An appending step also keeps its new-page array (padded to 32 bytes) and
-  // copies of at most one 32-byte row per row of the work list in the slot.
-  const uint64_t pages = (uint64_t(max_num_seqs) * 4 + 31) / 32 * 32;
-  const uint64_t slot = (work_bytes + pages + work_bytes + 4095) / 4096 * 4096;
+  const uint64_t slot = need.slot;
   bool small = false;
   for (auto& p : r->ring) small = small || p.bytes < slot;
   if (!small) return SF_OK;

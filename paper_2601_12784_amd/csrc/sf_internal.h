@@ -34,12 +34,14 @@ constexpr int32_t kSharedGroups = SF_PLAN_SHARED_GROUPS;
 enum class StepKind { kPlain = 0, kFp8 = 1, kAppend = 2 };
 sf_status decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_lens_host, const sf_plan_opts* opts, StepKind kind,
                              int32_t* work_host, uint64_t work_capacity_bytes, sf_plan_info* info);
-// The most partial results and work-list rows that decode_plan_runner's
-// segments of pairs take for any batch of at most num_seqs sequences.
-struct PairPlanMost {
-  int64_t partials, rows;
+// What sf_runner_reserve takes: device memory (workspace and device copies of
+// rows) and a ring slot, for the plan that the caller names and for any plan
+// that decode_plan_runner makes for at most num_seqs sequences, of every kind.
+struct ReserveBytes {
+  uint64_t device, slot;
 };
-PairPlanMost pair_plan_most(const sf_attn_desc* shape, const sf_plan_opts* opts, int32_t num_seqs);
+ReserveBytes reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
+                           uint64_t work_bytes, int32_t num_seqs);
 inline int64_t table_rows(int64_t workers) { return workers; }   // worker-table rows of a plan
 uint64_t desc_key(const sf_attn_desc* d);
 uint64_t align256(uint64_t x);

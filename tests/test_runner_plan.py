@@ -118,23 +118,45 @@ def test_shared_groups_are_the_runners_alone():
                                   1 << 30, None) == 4
 
 
-def test_smaller_batches_fit_what_a_large_one_reserves():
-    """sf_runner_reserve's floor, re-derived: segments of pairs take at most 4 per
-    CU (8 where the pairs alone are more than 4 per CU) and 8 workers per CU,
-    whatever the batch; its four times the reserved rows covers every batch that
-    the reserved one shrinks to."""
+def reserved(full, hq, hkv, d, kind, seqs, **opts):
+    """Bytes (device, slot) that a reserve for the batch `full`, planned as a step of `kind`, sees to."""
+    desc, info, _ = runner_plan(full, hq, hkv, d, kind, **opts)
+    got = np.zeros(2, np.uint64)
+    assert B.lib().sf_debug_runner_reserve(ctypes.byref(desc), ctypes.byref(B.make_opts(**opts)), info.workspace_bytes,
+                                           info.work_bytes, seqs, got.ctypes.data) == 0
+    return got.tolist()
+
+
+def taken(lens, hq, hkv, d, kind, **opts):
+    """Bytes (device, slot) that a step takes, at most."""
+    _, info, rows = runner_plan(lens, hq, hkv, d, kind, **opts)
+    append = kind == 2
+    pages = (len(lens) * 4 + 31) // 32 * 32 if append else 0
+    items = rows[info.num_workers: info.num_workers + info.num_work]
+    single = int((items[:, 5] < 0).sum()) if append else 0
+    al = lambda x: -(-x // 256) * 256   # noqa: E731
+    return [al(info.workspace_bytes) + (info.num_combine + single) * 32 + pages,
+            info.work_bytes + (info.num_work * 32 if append else 0) + pages]
+
+
+def test_smaller_batches_and_other_kinds_fit_what_a_large_one_reserves():
+    """Over all kinds of the reserve and of the step, for batches of the same
+    sequences and for fewer and shorter ones; with batches that are planned as
+    whole pairs for one kind and as slices with many partial results for another
+    or for a part of them."""
     rng = np.random.default_rng(3)
-    cus = 256
-    for trial in range(200):
-        hkv = int(rng.choice([1, 2, 4, 8]))
-        n = int(rng.choice([1, 3, 17, 64, 140, 200, 520, 1030]))
-        full = rng.integers(1, int(rng.choice([40, 600, 4000, 20000])), n)
-        _, large, _ = runner_plan(full, 4 * hkv, hkv, 128)
-        for _ in range(4):
-            lens = np.minimum(full, rng.integers(0, full.max() + 1, n) if rng.random() < .5 else rng.integers(1, full.max() + 1))
-            lens = rng.permutation(lens)[: int(rng.integers(1, n + 1))]
-            _, info, _ = runner_plan(lens, 4 * hkv, hkv, 128)
-            segments = 8 * cus if n * hkv > 4 * cus else 4 * cus
-            rows = 8 * cus + segments + min(n * hkv, segments // 2)
-            assert info.work_bytes <= max(large.work_bytes, min(rows * 32, 4 * large.work_bytes)), (trial, lens)
-            assert info.num_partials <= max(large.num_partials, segments), (trial, lens)
+    trials = [(int(rng.choice([1, 3, 17, 64, 140, 200, 520, 1030])), int(rng.choice([1, 2, 4, 8])),
+               int(rng.choice([40, 600, 4000, 20000]))) for _ in range(150)] + [(200, 4, 600)] * 60
+    for trial, (n, hkv, top) in enumerate(trials):
+        full = rng.integers(1, top, n)
+        opts = {} if trial % 5 else dict(workers_per_cu=int(rng.integers(1, 9)))
+        room = np.array([reserved(full, 4 * hkv, hkv, 128, kind, n, **opts) for kind in range(3)]).min(0)
+        for part in range(4):
+            lens = full
+            if part:
+                lens = np.minimum(full, rng.integers(0, full.max() + 1, n) if rng.random() < .5 else rng.integers(1, full.max() + 1))
+                lens = rng.permutation(lens)[: int(rng.integers(max(1, n * (part - 1) // 3), n + 1))]
+            if lens.max() == 0:
+                continue
+            for kind in range(3):
+                assert np.all(np.array(taken(lens, 4 * hkv, hkv, 128, kind, **opts)) <= room), (trial, part, kind, lens.tolist())
