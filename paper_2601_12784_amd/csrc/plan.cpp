@@ -13,6 +13,8 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "sf_internal.h"
@@ -431,6 +433,8 @@ double runner_estimate(const RunnerCost& c, int64_t total, int64_t workers, int6
          (partials > 0 ? c.merge + kPartialUs * double(partials) + kDepthUs * double(std::max<int64_t>(0, depth - kDepth)) : 0.0);
 }
 
+int32_t pages_of(int32_t tokens) { return int32_t((int64_t(tokens) + kPage - 1) / kPage); }
+
 bool slices_left_to_planner(const sf_plan_opts& o) {
   return o.chunk_pages == 0 && o.workers_per_cu == 0 && o.min_chunk_pages == 0 && o.xcd_parity_skew == 0 && o.num_cus >= 0;
 }
@@ -452,35 +456,51 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   const int64_t cus = o.num_cus ? o.num_cus : kDefaultNumCus;
   const int64_t hkv = desc->num_kv_heads, g = desc->num_q_heads / hkv;
   const int32_t B = desc->num_seqs;
-  int64_t total = 0, empty = 0;
+  // Pages of the sequences that have any, as floats (exact below kExact).
+  constexpr int64_t kExact = int64_t(1) << 23;
+  const std::unique_ptr<float[]> pages(new (std::nothrow) float[size_t(B)]);
+  if (!pages) return slices();
+  int64_t total = 0, longest_pair = 0;
+  int32_t some = 0;
   for (int32_t s = 0; s < B; ++s) {
     const int32_t L = seq_lens_host[s];
     if (L < 0 || (L > 0 && desc->num_pages == 0)) return SF_ERR_INVALID_ARG;
-    const int64_t npg = (int64_t(L) + kPage - 1) / kPage;
+    const int64_t npg = pages_of(L);
     if (npg > desc->block_table_stride) return SF_ERR_INVALID_ARG;
     total += npg * hkv;
-    empty += npg == 0 ? hkv : 0;
+    longest_pair = std::max(longest_pair, npg);
+    pages[some] = float(npg);
+    some += npg > 0;
   }
-  const int64_t pairs = int64_t(B) * hkv - empty;
-  if (total == 0 || total > kRunnerPages * 4 * cus || pairs + empty > 8 * cus) return slices();
+  const int64_t pairs = some * hkv, empty = int64_t(B) * hkv - pairs;
+  if (total == 0 || total > kRunnerPages * 4 * cus || pairs + empty > 8 * cus || longest_pair >= kExact) return slices();
 
   // Segments of at most `most` pages: their number (an empty pair is one), the
-  // cut pairs and their segments.
+  // cut pairs and their segments. The search below counts several dozen times
+  // at most, each on the critical path of a step: without a division per
+  // sequence, in a loop that the compiler turns into vector code.
   struct Count {
     int64_t segments = 0, cut = 0, partials = 0, longest = 0;
   };
-  auto count = [&](int32_t most) {
-    Count c;
-    for (int32_t s = 0; s < B; ++s) {
-      const int32_t n = (seq_lens_host[s] + kPage - 1) / kPage;
-      const int32_t k = n <= most ? 1 : (n + most - 1) / most;
-      c.segments += k;
-      if (k > 1) ++c.cut, c.partials += k;
-      c.longest = std::max<int64_t>(c.longest, (n + k - 1) / k);
+  auto count = [&](int64_t most) {
+    const float m = float(most), inv = 1.f / m;
+    int32_t segments = 0, cut = 0, longest = 0;
+    for (int32_t s = 0; s < some; ++s) {
+      const float n = pages[s];
+      float q = float(int32_t((n - 1.f) * inv));          // floor((n - 1) / most), or one off:
+      const float rem = (n - 1.f) - q * m;                // whole numbers below kExact, so exact
+      q += rem >= m ? 1.f : 0.f;
+      q -= rem < 0.f ? 1.f : 0.f;
+      const float length = n / (q + 1.f);                 // rounds to no other whole number
+      segments += int32_t(q) + 1;
+      cut += q > 0.f ? 1 : 0;
+      longest = std::max(longest, int32_t(length) + (float(int32_t(length)) < length ? 1 : 0));
     }
-    c.segments *= hkv;
-    c.cut *= hkv;
-    c.partials *= hkv;
+    Count c;
+    c.segments = segments * hkv + empty;
+    c.cut = cut * hkv;
+    c.partials = (int64_t(segments) - (some - cut)) * hkv;
+    c.longest = longest;
     return c;
   };
   const RunnerCost cost = {(fp8 ? 0.75 : 0.95) * (desc->head_dim == 64 ? 0.75 : 1.0),
@@ -491,45 +511,77 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   const int64_t wpc = o.workers_per_cu ? o.workers_per_cu : kDefaultWorkersPerCu;
   const int64_t slice_workers = std::min<int64_t>(wpc * cus, (total + kDefaultMinChunk - 1) / kDefaultMinChunk);
   const int64_t slice = (total + slice_workers - 1) / slice_workers;
-  int64_t most_segments = 1, window = 0, window_pairs = 0, longest_pair = 0;
+  int64_t most_segments = 1, window = 0, window_pairs = 0;
   bool whole_pairs = total % slice_workers == 0;   // every slice is one pair
-  for (int32_t s = 0, first = 0; s < B; ++s) {
-    const int64_t n = (seq_lens_host[s] + kPage - 1) / kPage;
-    if (n == 0) continue;
+  for (int32_t s = 0, first = 0; s < some; ++s) {
+    const int64_t n = int64_t(pages[s]);
     whole_pairs = whole_pairs && n == slice;
-    longest_pair = std::max(longest_pair, n);
     window += n * hkv;
     window_pairs += hkv;
     while (window > slice && first < s) {
-      const int64_t m = (seq_lens_host[first] + kPage - 1) / kPage;
-      if (m > 0) window -= m * hkv, window_pairs -= hkv;
-      ++first;
+      window -= int64_t(pages[first++]) * hkv;
+      window_pairs -= hkv;
     }
-    most_segments = std::max(most_segments, window <= slice ? window_pairs + 1 : std::min(hkv, slice / n) + 1);
+    // (slice / n: both below 2^31, as slice < n hkv here)
+    most_segments = std::max(most_segments, window <= slice ? window_pairs + 1
+                                            : n > slice     ? 1
+                                                            : std::min<int64_t>(hkv, int32_t(slice) / int32_t(n)) + 1);
   }
   double best_us = runner_estimate(cost, total, slice_workers, slice, whole_pairs ? 0 : most_segments - 1,
                                    whole_pairs ? 0 : slice_workers + std::min(pairs, slice_workers), longest_pair / slice + 1);
   int32_t best = 0, waves = 1;
   Count chosen;
+  struct Found {
+    int64_t target = 0, least = 0, most = 0;
+    Count c;
+  } seen[12];   // cuts found so far (the group sizes share targets)
+  int32_t num_seen = 0;
   for (const int32_t g8 : {1, 2, 4, 8}) {
     if ((pairs + empty) * g8 > 8 * cus) break;
     int64_t last = 0;
-    auto consider = [&](int64_t most) {
+    auto consider = [&](int64_t most, const Count& c) {
       if (most == last) return;
       last = most;
-      const Count c = count(int32_t(most));
       const double us = runner_estimate(cost, total, c.segments * g8, (c.longest + g8 - 1) / g8, 0, c.partials,
                                         (longest_pair + most - 1) / most, g8);
       if (us < best_us) best_us = us, best = int32_t(most), waves = g8, chosen = c;
     };
-    consider(longest_pair);   // every pair whole
-    for (const int64_t target : {2 * cus, 4 * cus, 8 * cus}) {
-      // the shortest segments that take at most `target` waves; more than four
-      // waves per CU only where the pairs alone need them
-      if ((pairs + empty) * g8 > target || (target > 4 * cus && (pairs + empty) * g8 <= 4 * cus)) continue;
-      int64_t most = std::max<int64_t>(g8, (total * g8 + target - 1) / target);
-      while (count(int32_t(most)).segments * g8 > target) most += std::max<int64_t>(1, most / 32);
-      consider(std::min(most, longest_pair));
+    Count whole;
+    whole.segments = pairs + empty;
+    whole.longest = longest_pair;
+    consider(longest_pair, whole);
+    for (int32_t r = 1; r <= 3; ++r) {
+      // the shortest segments that take at most `target` waves, within 1/32;
+      // more than four waves per CU only where the pairs alone need them
+      const int64_t target = (cus << r) / g8;   // workgroups
+      if (pairs + empty > target || (r == 3 && (pairs + empty) * g8 <= 4 * cus)) continue;
+      const int64_t least = std::max<int64_t>(g8, (total + target - 1) / target);
+      if (least >= longest_pair) continue;   // no pair would be cut
+      // no plan with a merge beats the stream of the batch's bytes and the merge
+      if (kStreamUs + double(total) * cost.bytes / (cost.gbytes * 1e3) + cost.merge >= best_us) continue;
+      bool found = false;
+      for (const Found& f : seen)
+        if (f.target == target && f.least <= least && least <= f.most) consider(f.most, f.c), found = true;
+      if (found) continue;
+      // About A + B / m segments of at most m pages: each count moves one end of
+      // the bracket there, a little to the side that fits.
+      int64_t most = longest_pair, low = 0;
+      double low_segments = 0;
+      Count c = whole;
+      for (int64_t m = least;; ) {
+        const Count n = count(m);
+        if (n.segments <= target)
+          most = m, c = n;
+        else
+          low = m, low_segments = double(n.segments);
+        if (low == 0 || most - low <= std::max<int64_t>(1, low / 32)) break;
+        const double b = (low_segments - double(c.segments)) / (1.0 / double(low) - 1.0 / double(most));
+        const double at = b / (double(target) - low_segments + b / double(low));
+        const int64_t gap = std::max<int64_t>(1, (most - low) / 8);
+        m = std::min(most - gap, std::max(low + gap, int64_t(std::min(at * 1.02, double(most))) + 1));
+      }
+      seen[num_seen++] = {target, least, most, c};
+      consider(most, c);
     }
   }
   if (best == 0) return slices();
@@ -557,7 +609,7 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   int32_t* comb = items + work * kItemInts;
   int32_t item = 0, slot = 0, cut = 0;
   for (int32_t s = 0; s < B; ++s) {
-    const int32_t L = seq_lens_host[s], n = (L + kPage - 1) / kPage;
+    const int32_t L = seq_lens_host[s], n = pages_of(L);
     const int32_t k = n <= best ? 1 : (n + best - 1) / best;
     for (int32_t h = 0; h < hkv; ++h) {
       if (k > 1) {

@@ -3,6 +3,7 @@ pair in exactly one segment, rows that fit together as the kernels read them,
 and sf_decode_attn_plan's own plan wherever the caller chose the slices or the
 batch has many pages per worker."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -28,6 +29,9 @@ def runner_plan(lens, hq, hkv, d, kind=0, **opts):
 
 CASES = [([17, 64, 130, 300], 4, 1, 64), ([32768], 28, 4, 128), ([1000], 28, 4, 128), ([1, 0, 16, 17, 0, 33], 8, 8, 128),
          ([5] * 300, 28, 4, 128), ([600] * 64, 40, 8, 128), ([1] + [0] * 40, 16, 1, 64)]
+# lengths that are whole multiples of the segments that a search may try, and one long pair among many
+CASES += [([16 * 24 * (i % 9 + 1) for i in range(150)], 4, 1, 64), ([16 * 7] * 600 + [16 * 2100], 16, 1, 128),
+          ([655360 - 16 * 200] + [16] * 100, 16, 1, 128)]
 CASES += [(rng.integers(0, int(hi), int(n)).tolist(), hkv * g, hkv, d)
           for rng in [np.random.default_rng(8)] for _ in range(30)
           for hi, n, hkv, g, d in [(rng.choice([40, 300, 5000]), rng.integers(1, 400), int(rng.integers(1, 9)),
@@ -83,6 +87,34 @@ def test_plan_covers_every_page_once(case, kind):
     g = hq // hkv
     al = lambda x: -(-x // 256) * 256   # noqa: E731
     assert info.workspace_bytes == (al(info.num_partials * g * d * 4) + al(info.num_partials * g * 4) if slots else 0)
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("case", ["lognormal", "two_long", "many", "heads"])
+def test_search_costs_little_next_to_the_slices(case, kind):
+    """The search for a cut is on the critical path of every step: skewed batches
+    with few KV heads, where it counts most, take no more than four times the
+    plan of equal slices (1 to 2.2 times measured; 4 to 12 times when every
+    candidate was a pass with a division per sequence). Least of 30 runs each."""
+    rng = np.random.default_rng(0)
+    ln = lambda n, m: np.clip(np.exp(np.log(m) + rng.standard_normal(n)), max(1, m // 8), 16 * m)   # noqa: E731
+    lens, hq, hkv, d = {"lognormal": (ln(512, 500), 16, 1, 128), "two_long": (np.r_[rng.integers(1, 200, 510), 30000, 30000], 16, 1, 128),
+                        "many": (ln(1000, 200), 16, 1, 128), "heads": (ln(128, 500), 14, 2, 64)}[case]
+    lens = lens.astype(np.int32)
+    desc = B.make_desc(lens.size, hq, hkv, d, int(lens.max() // 16 + 1), 1 << 20, 0.1)
+    info, L, work = B.sf_plan_info(), B.lib(), np.empty(1 << 18, np.int32)
+    opts, slices = B.make_opts(), B.make_opts(workers_per_cu=8 if kind == 1 else 0)
+    best = [1.0, 1.0]
+    for _ in range(30):
+        t = time.perf_counter()
+        assert L.sf_decode_attn_plan(ctypes.byref(desc), lens.ctypes.data, ctypes.byref(slices), work.ctypes.data, work.nbytes,
+                                     ctypes.byref(info)) == 0
+        u = time.perf_counter()
+        assert L.sf_runner_plan(ctypes.byref(desc), lens.ctypes.data, ctypes.byref(opts), kind, work.ctypes.data, work.nbytes,
+                                ctypes.byref(info)) == 0
+        best = [min(best[0], u - t), min(best[1], time.perf_counter() - u)]
+    print(f"{case} {kind}: slices {best[0] * 1e6:.1f} us, runner {best[1] * 1e6:.1f} us")
+    assert best[1] < 4 * best[0]
 
 
 @pytest.mark.parametrize("opts", [dict(chunk_pages=3), dict(workers_per_cu=4), dict(min_chunk_pages=8),
