@@ -1,7 +1,8 @@
 """The merge of pairs cut into many segments (one workgroup per pair and head),
 at segment counts around its threshold (4 per pair) and its slices (8 at
 head_dim 128, 16 at 64), against the fp64 oracle: |gpu - ref| <= 2e-3 + 1e-2 |ref|
-for out and lse, pools and block tables bit for bit.
+for out and lse, and in the 2-norm at the precision of the weights and sums
+(test_gpu_short_batches.py); pools and block tables bit for bit.
 
 One-page slices (chunk_pages = 1) make a sequence of n pages n segments. The
 appending steps pass through a step whose newest token opens a page: its
@@ -13,6 +14,7 @@ import oracle
 from paper_2601_12784_amd import binding as B
 from paper_2601_12784_amd.workloads import PAGE, bf16_bits, build_batch, make_decode_loop
 from test_gpu_append import assert_close, run_loop
+from test_gpu_short_batches import assert_near
 
 pytestmark = pytest.mark.gpu
 SHAPES = [(28, 4, 128), (4, 1, 64), (16, 1, 128), (3, 3, 64)]
@@ -43,6 +45,7 @@ def test_merge_of_many_segments(shape, segments):
                                       b.seq_lens, b.scale)
     assert_close(out.cpu().numpy(), ref_o, "out")
     assert_close(lse.cpu().numpy(), ref_l, "lse")
+    assert_near(out.cpu().numpy(), lse.cpu().numpy(), (ref_o, ref_l), f"{shape} {segments}")
 
 
 @pytest.mark.parametrize("segments", [4, 8, 17])

@@ -27,6 +27,38 @@ def runner_plan(lens, hq, hkv, d, kind=0, **opts):
     return desc, info, work[:-8].reshape(-1, 8)
 
 
+def spread(n, lo, hi):
+    """n lengths from lo to hi, evenly."""
+    return np.linspace(lo, hi, n).astype(np.int32)
+
+
+# (kind, head_dim, waves per workgroup, lens, heads): a plan of shared groups of every size that the kernels are built
+# for, with whole pairs and with cut ones (groups of 8 leave none to cut)
+SHARED_CASES = [
+    (0, 64, 2, spread(2, 10, 100), (3, 3)), (0, 64, 2, spread(4, 183, 1831), (3, 3)),
+    (0, 64, 4, spread(1, 161, 179), (3, 3)), (0, 64, 4, spread(2, 90, 903), (3, 3)), (0, 64, 8, spread(1, 453, 504), (3, 3)),
+    (0, 128, 2, spread(1, 81, 162), (8, 2)), (0, 128, 2, spread(17, 62, 629), (8, 2)),
+    (0, 128, 4, spread(1, 129, 129), (8, 2)), (0, 128, 4, spread(1, 786, 874), (8, 2)), (0, 128, 8, spread(1, 323, 359), (8, 2)),
+    (1, 64, 2, spread(1, 129, 129), (3, 3)), (1, 64, 2, spread(5, 109, 1093), (3, 3)),
+    (1, 64, 4, spread(1, 225, 225), (3, 3)), (1, 64, 4, spread(2, 119, 1191), (3, 3)), (1, 64, 8, spread(1, 584, 584), (3, 3)),
+    (1, 128, 2, spread(1, 99, 111), (8, 2)), (1, 128, 2, spread(12, 90, 901), (8, 2)),
+    (1, 128, 4, spread(1, 163, 326), (8, 2)), (1, 128, 4, spread(1, 898, 898), (8, 2)), (1, 128, 8, spread(1, 450, 450), (8, 2)),
+    (2, 64, 2, spread(2, 10, 100), (3, 3)), (2, 64, 2, spread(9, 16, 167), (8, 8)),
+    (2, 64, 4, spread(1, 161, 179), (3, 3)), (2, 64, 4, spread(1, 258, 2580), (3, 3)), (2, 64, 8, spread(80, 1147, 1147), (3, 3)),
+    (2, 128, 2, spread(1, 81, 162), (8, 2)), (2, 128, 2, spread(2, 19, 193), (8, 2)),
+    (2, 128, 4, spread(1, 129, 129), (8, 2)), (2, 128, 4, spread(1, 193, 1932), (8, 2)), (2, 128, 8, spread(87, 460, 512), (8, 2)),
+    # the widest groups of query heads, many sequences
+    (0, 128, 8, np.arange(100, 600, 8, dtype=np.int32), (28, 4)), (1, 64, 8, spread(27, 657, 807), (8, 8)),
+    (2, 64, 8, spread(255, 1911, 2013), (4, 1)), (0, 64, 4, spread(239, 226, 418), (4, 1)), (0, 128, 4, spread(1, 1000, 1000), (16, 1)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SHARED_CASES)))
+def test_shared_cases_share(case):
+    kind, d, group, lens, (hq, hkv) = SHARED_CASES[case]
+    assert runner_plan(lens, hq, hkv, d, kind)[1].workers_per_group == SHARED + group
+
+
 CASES = [([17, 64, 130, 300], 4, 1, 64), ([32768], 28, 4, 128), ([1000], 28, 4, 128), ([1, 0, 16, 17, 0, 33], 8, 8, 128),
          ([5] * 300, 28, 4, 128), ([600] * 64, 40, 8, 128), ([1] + [0] * 40, 16, 1, 64)]
 # lengths that are whole multiples of the segments that a search may try, and one long pair among many
