@@ -405,7 +405,7 @@ sf_status sf_extend_attn_plan(const sf_attn_desc* desc, const int32_t* seq_lens_
  * for position p = P_s + j, before the attention reads them; the pools are
  * then written, and the block table must already hold every page the new
  * tokens land in. With both NULL the pool must already hold them. One
- * launch of the attention kernel follows (one 512-thread block per item).
+ * launch of the attention kernel follows (one 768-thread block per item).
  * Numerics: scores from bf16 q and K with fp32 accumulation; the softmax
  * weights and the values enter the P.V product as fp16, with fp32
  * accumulation. Every bf16 V element of magnitude in [2^-17, 65280] is exact

@@ -309,6 +309,11 @@ sf_status sf::extend_plan_parts(const sf_attn_desc* desc, const int32_t* seq_len
   if (store)
     for (int32_t s = 0; s < desc->num_seqs; ++s)
       if (news[s] > 0) store_pages += pages_of(lens[s]) - (lens[s] - news[s]) / kPage;
+  // Runs of 4 pages above 2048 keep the list, and the slots that hold it, a
+  // quarter as long; the launch takes the same there (us at runs of 1, 2, 4 and
+  // 8, 28/4 heads: 6016 pages 102, 106, 106, 102; 2000 pages 38, 36, 36, 43).
+  // Fewer pages want every workgroup: 504 pages 12, 10, 13, 21, 63 pages 7.2,
+  // 9.5, 13, 22.
   const int32_t run = store_pages > 2048 ? 4 : 1;
   if (store)
     for (int32_t s = 0; s < desc->num_seqs; ++s)

@@ -11,7 +11,10 @@
 // all new tokens after it, so the work runs on the matrix cores. A work item
 // is one (sequence, KV head, block of new tokens); its rows are the block's
 // tokens times the g query heads of the group (token-major), at most 384 rows,
-// 32 per wave (12 waves, three per SIMD). The item walks the keys in steps of
+// 32 per wave (12 waves, three per SIMD). Grids too short for that take items
+// of 128 rows (four waves, two workgroups per CU, staged two steps ahead) or
+// parts of key walks, whose partial results extend_merge_kernel joins; which,
+// the runner's plan decides. The item walks the keys in steps of
 // 32 (two pages), one step per barrier: eight of the waves stage the K and V
 // tiles of the next step (16 KiB at D = 128) through LDS, double buffered, and
 // each wave computes, per step and 16-row tile,
@@ -41,7 +44,8 @@
 // Measured alternatives (full re-prefill of 32 long-tail trajectories):
 // 64 rows per wave (4 waves, one per SIMD) halves the LDS operand reads but
 // leaves no second wave per SIMD to overlap with, and is 1.5x slower; items
-// of 128 rows double the K/V staging per row and are 2x slower; 16 rows per
+// of 128 rows triple the K/V staging per row and, on such a full grid, are 2x
+// slower; 16 rows per
 // wave (16 waves, four per SIMD) doubles the LDS operand reads per row and
 // is 12 % slower than three waves of 32 rows.
 #include <hip/hip_ext.h>

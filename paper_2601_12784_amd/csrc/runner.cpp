@@ -288,9 +288,6 @@ extern "C" sf_status sf_runner_step(sf_runner* r, const sf_attn_desc* desc, cons
   // launch's rows are one contiguous range, which the attention launch
   // copies to device memory (RowCopy).
   const uint64_t pages_bytes = append ? (uint64_t(desc->num_seqs) * 4 + 31) / 32 * 32 : 0;
-  // An fp8 block moves half the bytes of a bf16 one: unless the caller chose,
-  // fp8 steps plan two waves per SIMD (measured: kernel 129 us instead of 136
-  // on the long-tail batch; bf16 is slower at 8).
   sf_plan_info info;
   const sf::StepKind kind = fp8 ? sf::StepKind::kFp8 : append ? sf::StepKind::kAppend : sf::StepKind::kPlain;
   st = sf::decode_plan_runner(desc, seq_lens_host, &r->opts, kind, pin.ptr, pin.bytes, &info);
