@@ -646,7 +646,10 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
 //   segments of pairs (options left to the planner): at most 8 workers per CU,
 //     and as many segments where the pairs alone are more than 4 per CU, half
 //     as many otherwise (or where a workgroup's waves share a segment).
-// A forced slice size has no such bound: the caller's bytes stand alone.
+// A forced slice size has no such bound, and more than kReserveWorkers workers
+// are beyond what any batch here needs: the caller's bytes stand alone then.
+constexpr int64_t kReserveWorkers = 1 << 14;
+
 sf::ReserveBytes sf::reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
                                    uint64_t work_bytes, int32_t num_seqs) {
   const sf_plan_opts none = {};
@@ -662,14 +665,14 @@ sf::ReserveBytes sf::reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts
     if (appending) append_rows = std::max(append_rows, workers + 2 * segments + cut);
   };
   auto slices = [&](int64_t wpc, bool appending) {
-    const int64_t w = std::min<int64_t>(wpc * cus, INT32_MAX / 2), cut = std::min(pairs, w - 1);
-    plan(w, pairs + w - 1, w - 1 + cut, cut, appending);
+    const int64_t w = wpc * cus, cut = std::min(pairs, w - 1);
+    if (w <= kReserveWorkers) plan(w, pairs + w - 1, w - 1 + cut, cut, appending);
   };
   if (o.chunk_pages == 0) {
     slices(o.workers_per_cu ? o.workers_per_cu : kDefaultWorkersPerCu, true);
     if (o.workers_per_cu == 0) slices(kFp8WorkersPerCu, false);
     const int64_t segments = pairs > 4 * cus ? 8 * cus : 4 * cus;
-    if (slices_left_to_planner(o)) plan(8 * cus, segments, segments, std::min(pairs, segments / 2), true);
+    if (slices_left_to_planner(o) && 8 * cus <= kReserveWorkers) plan(8 * cus, segments, segments, std::min(pairs, segments / 2), true);
   }
   const uint64_t head_rows = uint64_t(partials) * (shape->num_q_heads / shape->num_kv_heads);
   workspace_bytes = std::max(workspace_bytes, align256(head_rows * shape->head_dim * 4) + align256(head_rows * 4));

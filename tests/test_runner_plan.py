@@ -224,3 +224,12 @@ def test_smaller_batches_and_other_kinds_fit_what_a_large_one_reserves():
                 continue
             for kind in range(3):
                 assert np.all(np.array(taken(lens, 4 * hkv, hkv, 128, kind, **opts)) <= room), (trial, part, kind, lens.tolist())
+
+
+def test_reserve_is_bounded_for_any_options():
+    """Worker counts beyond any batch's need do not become memory."""
+    desc, got = B.make_desc(0, 28, 4, 128, 1, 0, 1.0), np.zeros(2, np.uint64)
+    for opts in (dict(workers_per_cu=2**20), dict(num_cus=2**30), dict(num_cus=2**30, workers_per_cu=2**30), dict(chunk_pages=1)):
+        assert B.lib().sf_debug_runner_reserve(ctypes.byref(desc), ctypes.byref(B.make_opts(**opts)), 1000, 4096, 64,
+                                               got.ctypes.data) == 0
+        assert got.tolist() == [1024 + 4096 + 256, 12288]
