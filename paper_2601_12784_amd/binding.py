@@ -465,9 +465,11 @@ class _SharedScratch:
     BLOCKS = 4
 
     def __init__(self):
-        self._lock = threading.Lock()
+        self._lock = threading.RLock()   # a collection inside may drop an object
         self._blocks = {}   # (thread, device, stream) -> tensor, least recently used first
         self._live = 0
+        self._dead = []     # runners of dropped objects, with what they lent
+        self._capturing = torch.cuda.is_current_stream_capturing
 
     def join(self):
         with self._lock:
@@ -478,6 +480,21 @@ class _SharedScratch:
             self._live -= 1
             if self._live == 0:
                 self._blocks.clear()
+
+    def bury(self, destroy, runner, lent):
+        """Destroys a dropped object's runner, which waits for its calls before what
+        it lent may go. The wait would break a capture: then the next object sees to it."""
+        with self._lock:
+            self._dead.append((destroy, runner, lent))
+        if not self._capturing():
+            self.reap()
+
+    def reap(self):
+        while self._dead:
+            with self._lock:
+                dead = self._dead.pop() if self._dead else None
+            if dead is not None:
+                dead[0](dead[1])
 
     def get(self, device, stream):
         """The block of this thread and stream (the current one's handle), or None."""
@@ -532,7 +549,7 @@ class ExtendAttention:
         self._runner = ctypes.c_void_p()
         self._memory = sf_runner_memory()
         self._lent = []         # what _memory lends for longer than a call; before it, what calls may still use
-        self._large = True      # the last plan took the shared block; a new object looks for one
+        self._large = None      # a plan took the shared block (None: a new object looks for one)
         self._spare = [None, 0, None, 0, 0]   # pinned, device (offsets in bytes) and the bytes left for captured lists
         self._captured = []     # their lists (pinned, device), which graphs read
         self.last_info = None
@@ -556,6 +573,7 @@ class ExtendAttention:
                                                               ctypes.byref(self._runner)))
             self._L, self._scratch = L, _scratch
             _scratch.join()
+            _scratch.reap()
         self._lend(self.SLOT, self.DEVICE - self.SLOT, None)
 
     def _lend(self, slot, device, stream):
@@ -583,8 +601,8 @@ class ExtendAttention:
         m = self._memory
         need = (int(m.need_device) * 5 // 4 + 4096 + 255) // 256 * 256
         slot, device = int(m.pinned_bytes) // m.slots, int(m.device_bytes)
-        self._large = need > self.KEEP and self._ordered(stream)
-        if self._large:
+        if need > self.KEEP and self._ordered(stream):
+            self._large = True
             self._scratch.grow(torch.cuda.current_device(), _stream(None), need)
         else:
             device = max(device, need)
@@ -597,18 +615,19 @@ class ExtendAttention:
         """One sf_runner_extend, on the shared block where the last plan took more than is kept."""
         m = self._memory
         block = None
-        if self._large and self._ordered(stream):
+        if self._large is not False and self._ordered(stream):
             block = self._scratch.get(torch.cuda.current_device(), args[13])
         if block is None:
             st = self._L.sf_runner_extend(*args)
-            if len(self._lent) > 1 and st in (0, CAPACITY):   # calls on what was lent before have been waited for
-                del self._lent[:-1]
-            return st
-        kept = m.device, m.device_bytes
-        m.device, m.device_bytes, m.device_per_call = block.data_ptr(), block.numel(), 1
-        st = self._L.sf_runner_extend(*args)
-        m.device, m.device_bytes, m.device_per_call = *kept, 0
-        self._large = m.need_device > m.device_bytes
+        else:
+            kept = m.device, m.device_bytes
+            m.device, m.device_bytes, m.device_per_call = block.data_ptr(), block.numel(), 1
+            st = self._L.sf_runner_extend(*args)
+            m.device, m.device_bytes, m.device_per_call = *kept, 0
+        if self._large is None:
+            self._large = m.need_device > m.device_bytes
+        if len(self._lent) > 1 and st in (0, CAPACITY):   # other slots: calls on what was lent before have been waited for
+            del self._lent[:-1]
         return st
 
     def __call__(self, q, k_pool, v_pool, block_table, seq_lens, q_lens, scale, out=None, lse=None,
@@ -692,7 +711,7 @@ class ExtendAttention:
     def __del__(self):
         r = getattr(self, "_runner", None)
         if r is not None and r.value:
-            self._L.sf_runner_destroy(r)   # waits for the calls that use the lent memory
+            self._scratch.bury(self._L.sf_runner_destroy, r.value, self._lent)
             r.value = None
             self._scratch.leave()
 

@@ -240,6 +240,10 @@ extern "C" sf_status sf_runner_create(const sf_attn_desc* shape, const sf_plan_o
 // Teardown cannot report errors: every call is made, whatever the others return.
 extern "C" void sf_runner_destroy(sf_runner* r) {
   if (!r) return;
+  // a garbage collector may be here with any device current
+  int current = r->device;
+  (void)hipGetDevice(&current);
+  if (current != r->device) (void)hipSetDevice(r->device);
   // Steps not yet marked ran on the caller's stream, which may be gone by
   // now: nothing is recorded on it here, the device is waited for instead.
   if (r->unmarked < r->steps) (void)hipDeviceSynchronize();
@@ -257,6 +261,7 @@ extern "C" void sf_runner_destroy(sf_runner* r) {
     (void)hipDeviceSynchronize();
     (void)hipFree(r->workspace);
   }
+  if (current != r->device) (void)hipSetDevice(current);
   delete r;
 }
 

@@ -342,3 +342,26 @@ def test_a_new_objects_first_call_plans_once(lens, earlier):
     out = call(*args)
     torch.cuda.synchronize()
     assert not asked and (not earlier or torch.equal(out, want))
+
+
+def test_object_dropped_during_a_capture():
+    """Dropping an object waits for its calls, which a capture does not allow:
+    its runner goes with the next object instead."""
+    eb = build_extend([60], [60], 8, 2, 64, seed=2)
+    b = eb.batch
+    args = (eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens, eb.q_lens,
+            b.scale)
+    call, other = (B.ExtendAttention(8, 2, 64) for _ in range(2))
+    want = call(*args)
+    other(*args)
+    out = torch.zeros_like(want)
+    torch.cuda.synchronize()
+    other(*args)   # not waited for
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        del other
+        call(*args, out=out)
+    assert len(B._scratch._dead) == 1
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want) and torch.equal(B.ExtendAttention(8, 2, 64)(*args), want) and not B._scratch._dead
