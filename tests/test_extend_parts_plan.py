@@ -2,7 +2,6 @@
 new tokens in exactly one part, slots and merges that fit together, every page
 of new tokens stored once; and argument checks that need no device."""
 import ctypes
-import threading
 
 import numpy as np
 import pytest
@@ -125,26 +124,26 @@ def test_captured_calls_keep_their_lists():
     assert np.array_equal(ha.numpy(), a) and len(call._captured) == 2
 
 
-def test_shared_scratch_is_per_thread_and_stream_and_bounded():
+def test_shared_scratch_is_bounded_and_alternates():
     pool = B._SharedScratch()
     cpu = torch.device("cpu")
+    key = lambda stream, thread=0: (thread, cpu, stream)   # noqa: E731
     pool.join()
     pool.join()
-    pool.grow(cpu, 1, 1000)
-    a = pool.get(cpu, 1)
-    pool.grow(cpu, 1, 900)
-    assert pool.get(cpu, 1) is a and pool.get(cpu, 2) is None
-    seen = []
-    t = threading.Thread(target=lambda: seen.append(pool.get(cpu, 1)))
-    t.start()
-    t.join()
-    assert seen == [None]
+    pool.grow(key(1), 1024)
+    a, v = pool.get(key(1)), pool.version
+    pool.grow(key(1), 512)
+    assert pool.get(key(1)) is a and pool.get(key(2)) is None and pool.get(key(1, thread=7)) is None and pool.version != v
+    first, second = a.next(), a.next()
+    assert {first, second} == {a.memory.data_ptr(), a.memory.data_ptr() + 1024} and a.next() == first
+    assert a.nbytes == 1024 and a.memory.numel() == 2048
     for stream in (2, 3, 4):
-        pool.grow(cpu, stream, 100)
-    assert pool.get(cpu, 1) is a          # used last: stream 2 goes first
-    pool.grow(cpu, 5, 100)
-    assert pool.get(cpu, 2) is None and pool.get(cpu, 1) is a and len(pool._blocks) == pool.BLOCKS
+        pool.grow(key(stream), 256)
+    assert pool.get(key(1)) is a          # used last: stream 2 goes first
+    pool.grow(key(5), 256)
+    assert pool.get(key(2)) is None and pool.get(key(1)) is a and len(pool._blocks) == pool.BLOCKS
     pool.leave()
-    assert pool.get(cpu, 1) is a
+    assert pool.get(key(1)) is a
+    v = pool.version
     pool.leave()
-    assert not pool._blocks
+    assert not pool._blocks and pool.version != v
