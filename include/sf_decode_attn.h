@@ -283,6 +283,13 @@ void sf_runner_destroy(sf_runner* runner);
  * negative max_num_seqs, SF_ERR_HIP if an allocation fails. */
 sf_status sf_runner_reserve(sf_runner* runner, uint64_t workspace_bytes, uint64_t work_bytes,
                             int32_t max_num_seqs, void* stream);
+/* The same for steps over sequences of seq_lens_host (host int32 [num_seqs])
+ * tokens, of up to twice as many pages in all, and over fewer or shorter ones,
+ * with any options (chunk_pages too). Takes no more than such steps can use, where
+ * sf_runner_reserve, which does not know the lengths, keeps a few MB.
+ * SF_ERR_INVALID_ARG for NULL pointers or negative numbers, else as
+ * sf_runner_reserve. */
+sf_status sf_runner_reserve_batch(sf_runner* runner, const int32_t* seq_lens_host, int32_t num_seqs, void* stream);
 /* The plan of a runner's step (host only, arguments as sf_decode_attn_plan;
  * kind: 0 a plain step, 1 over an fp8 cache, 2 appending). With options that leave the slices to the planner
  * (chunk_pages, workers_per_cu, min_chunk_pages and xcd_parity_skew 0) and few
@@ -599,10 +606,12 @@ sf_status sf_route(const sf_cost_model* model, double mu, int32_t min_initial_ve
 
 /*
  * Test support: bytes[0] of device memory and bytes[1] per ring slot that
- * sf_runner_reserve sees to for a runner of that shape and options; host only.
+ * sf_runner_reserve (total_pages < 0) or sf_runner_reserve_batch (0 bytes, and
+ * the pages of all pairs) sees to for a runner of that shape and options; host
+ * only.
  */
 sf_status sf_debug_runner_reserve(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
-                                  uint64_t work_bytes, int32_t max_num_seqs, uint64_t* bytes);
+                                  uint64_t work_bytes, int32_t max_num_seqs, int64_t total_pages, uint64_t* bytes);
 
 /*
  * Test support: the plan sf_runner_extend makes for a device of num_cus

@@ -114,6 +114,7 @@ def lib():
                                         vp, vp, vp, vp, ctypes.c_uint64, vp]
     L.sf_runner_create.argtypes = [P(sf_attn_desc), P(sf_plan_opts), P(vp)]
     L.sf_runner_reserve.argtypes = [vp, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int32, vp]
+    L.sf_runner_reserve_batch.argtypes = [vp, vp, ctypes.c_int32, vp]
     L.sf_runner_reserve.restype = ctypes.c_int
     L.sf_runner_destroy.argtypes = [vp]
     L.sf_runner_destroy.restype = None
@@ -127,7 +128,8 @@ def lib():
     L.sf_extend_attn.argtypes = [P(sf_attn_desc), P(sf_extend_info), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.sf_runner_extend.argtypes = [vp, P(sf_attn_desc), vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, P(sf_runner_memory),
                                    vp, P(sf_extend_info)]
-    L.sf_debug_runner_reserve.argtypes = [P(sf_attn_desc), P(sf_plan_opts), ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int32, vp]
+    L.sf_debug_runner_reserve.argtypes = [P(sf_attn_desc), P(sf_plan_opts), ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int32,
+                                          ctypes.c_int64, vp]
     L.sf_debug_extend_plan.argtypes = [P(sf_attn_desc), vp, vp, ctypes.c_int32, ctypes.c_int32, vp, ctypes.c_uint64, vp]
     L.sf_runner_plan.argtypes = [P(sf_attn_desc), vp, P(sf_plan_opts), ctypes.c_int32, vp, ctypes.c_uint64,
                                  P(sf_plan_info)]
@@ -154,7 +156,7 @@ def lib():
                "sf_page_pool_release", "sf_page_table_step", "sf_route", "sf_extend_attn_plan",
                "sf_extend_attn", "sf_decode_attn_fp8", "sf_kv_quantize_fp8", "sf_runner_create",
                "sf_runner_step", "sf_runner_extend", "sf_runner_plan", "sf_debug_extend_plan",
-               "sf_debug_runner_reserve", "sf_debug_stream_read", "sf_decode_attn_scratch"):
+               "sf_debug_runner_reserve", "sf_runner_reserve_batch", "sf_debug_stream_read", "sf_decode_attn_scratch"):
         getattr(L, fn).restype = ctypes.c_int
     L.sf_status_string.argtypes = [ctypes.c_int]
     L.sf_status_string.restype = ctypes.c_char_p
@@ -951,7 +953,9 @@ class DecodeAttention:
     def reserve(self, seq_lens, num_pages, block_table_stride, chunk_pages=None, fp8=False, stream=None):
         """Sizes the native runner's workspace and work-list ring for a step
         over seq_lens (the largest batch to come) ahead of the steps, so no
-        step stalls to grow them (sf_runner_reserve)."""
+        step stalls to grow them (sf_runner_reserve_batch): steps of any kind,
+        over these sequences, with up to twice the pages, or over fewer or
+        shorter ones."""
         lens = np.ascontiguousarray(seq_lens, dtype=np.int32)
         desc = make_desc(lens.size, self.hq, self.hkv, self.d, block_table_stride, num_pages, 1.0)
         o = self.opts
@@ -962,8 +966,8 @@ class DecodeAttention:
         _check("sf_runner_plan", st)
         main = stream or torch.cuda.current_stream(self.device)
         with torch.cuda.device(self.device):
-            _check("sf_runner_reserve", self.L.sf_runner_reserve(self._runner(chunk_pages), info.workspace_bytes,
-                                                                 info.work_bytes, lens.size, main.cuda_stream))
+            _check("sf_runner_reserve_batch", self.L.sf_runner_reserve_batch(self._runner(chunk_pages), lens.ctypes.data,
+                                                                             lens.size, main.cuda_stream))
 
     def __call__(self, q, k_pool, v_pool, block_table, seq_lens, scale, out=None, lse=None,
                  chunk_pages=None, stream: torch.cuda.Stream | None = None, attn_events=None,

@@ -638,20 +638,23 @@ sf_status sf::decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_le
   return SF_OK;
 }
 
-// A batch of at most num_seqs sequences, whatever its lengths and the kind of
-// its step, is planned as one of
+// A batch of at most num_seqs sequences and total_pages pages (of all its pairs;
+// < 0: any number), whatever the kind of its step, is planned as one of
 //   equal slices: at most W workers (the options' per CU; left to the planner,
-//     kDefaultWorkersPerCu, or kFp8WorkersPerCu over an fp8 cache). Each of the
-//     W - 1 boundaries between them adds a segment to a pair and may cut it;
-//   segments of pairs (options left to the planner): at most 8 workers per CU,
-//     and as many segments where the pairs alone are more than 4 per CU, half
-//     as many otherwise (or where a workgroup's waves share a segment).
-// A forced slice size has no such bound, and more than kReserveWorkers workers
-// are beyond what any batch here needs: the caller's bytes stand alone then.
+//     kDefaultWorkersPerCu, or kFp8WorkersPerCu over an fp8 cache; no more than
+//     one per smallest slice). Each of the W - 1 boundaries between them adds a
+//     segment to a pair and may cut it;
+//   segments of pairs (options left to the planner): at most 8 workers per CU
+//     and 8 per pair and page, and at most one segment per pair and page, 8 per
+//     CU where the pairs alone are more than 4 per CU, 4 per CU otherwise (or
+//     where a workgroup's waves share a segment).
+// Without total_pages a forced slice size has no such bound, and more than
+// kReserveWorkers workers are beyond what any batch here needs: the caller's
+// bytes stand alone then.
 constexpr int64_t kReserveWorkers = 1 << 14;
 
 sf::ReserveBytes sf::reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
-                                   uint64_t work_bytes, int32_t num_seqs) {
+                                   uint64_t work_bytes, int32_t num_seqs, int64_t total_pages) {
   const sf_plan_opts none = {};
   const sf_plan_opts& o = opts ? *opts : none;
   const int64_t cus = o.num_cus > 0 ? o.num_cus : kDefaultNumCus;
@@ -664,15 +667,26 @@ sf::ReserveBytes sf::reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts
     rows = std::max(rows, workers + segments + cut);
     if (appending) append_rows = std::max(append_rows, workers + 2 * segments + cut);
   };
-  auto slices = [&](int64_t wpc, bool appending) {
-    const int64_t w = wpc * cus, cut = std::min(pairs, w - 1);
-    if (w <= kReserveWorkers) plan(w, pairs + w - 1, w - 1 + cut, cut, appending);
+  const bool known = total_pages >= 0;
+  auto slices = [&](int64_t w, int64_t least, bool appending) {
+    if (known)
+      w = std::max<int64_t>(1, std::min(w, (total_pages + least - 1) / least));
+    else if (w > kReserveWorkers)
+      return;
+    const int64_t cut = std::min(pairs, w - 1);
+    plan(w, pairs + w - 1, w - 1 + cut, cut, appending);
   };
-  if (o.chunk_pages == 0) {
-    slices(o.workers_per_cu ? o.workers_per_cu : kDefaultWorkersPerCu, true);
-    if (o.workers_per_cu == 0) slices(kFp8WorkersPerCu, false);
-    const int64_t segments = pairs > 4 * cus ? 8 * cus : 4 * cus;
-    if (slices_left_to_planner(o) && 8 * cus <= kReserveWorkers) plan(8 * cus, segments, segments, std::min(pairs, segments / 2), true);
+  if (o.chunk_pages > 0) {
+    slices(INT64_MAX, o.chunk_pages, true);
+  } else {
+    const int64_t least = o.min_chunk_pages ? o.min_chunk_pages : kDefaultMinChunk;
+    slices((o.workers_per_cu ? o.workers_per_cu : kDefaultWorkersPerCu) * cus, least, true);
+    if (o.workers_per_cu == 0) slices(kFp8WorkersPerCu * cus, least, false);
+    if (slices_left_to_planner(o) && (known || 8 * cus <= kReserveWorkers)) {
+      const int64_t each = known ? total_pages + pairs : INT64_MAX / 8;
+      const int64_t segments = std::min(pairs > 4 * cus ? 8 * cus : 4 * cus, each);
+      plan(std::min(8 * cus, 8 * each), segments, segments, std::min(pairs, segments / 2), true);
+    }
   }
   const uint64_t head_rows = uint64_t(partials) * (shape->num_q_heads / shape->num_kv_heads);
   workspace_bytes = std::max(workspace_bytes, align256(head_rows * shape->head_dim * 4) + align256(head_rows * 4));
@@ -686,9 +700,9 @@ sf::ReserveBytes sf::reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts
 
 extern "C" sf_status sf_debug_runner_reserve(const sf_attn_desc* shape, const sf_plan_opts* opts,
                                              uint64_t workspace_bytes, uint64_t work_bytes, int32_t max_num_seqs,
-                                             uint64_t* bytes) {
+                                             int64_t total_pages, uint64_t* bytes) {
   if (!shape || !bytes || max_num_seqs < 0 || shape->num_kv_heads <= 0) return SF_ERR_INVALID_ARG;
-  const ReserveBytes b = reserve_bytes(shape, opts, workspace_bytes, work_bytes, max_num_seqs);
+  const ReserveBytes b = reserve_bytes(shape, opts, workspace_bytes, work_bytes, max_num_seqs, total_pages);
   bytes[0] = b.device;
   bytes[1] = b.slot;
   return SF_OK;

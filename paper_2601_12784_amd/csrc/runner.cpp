@@ -491,13 +491,9 @@ extern "C" sf_status sf_runner_extend(sf_runner* r, const sf_attn_desc* desc, co
   return SF_OK;
 }
 
-extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, uint64_t work_bytes,
-                                       int32_t max_num_seqs, void* stream) {
-  if (!r || max_num_seqs < 0) return SF_ERR_INVALID_ARG;
-  hipStream_t main = static_cast<hipStream_t>(stream);
-  // A smaller batch, or a step of another kind, may be planned in another way
-  // than the batch reserved for and take more than it.
-  const sf::ReserveBytes need = sf::reserve_bytes(&r->shape, &r->opts, workspace_bytes, work_bytes, max_num_seqs);
+namespace {
+
+sf_status reserve(sf_runner* r, const sf::ReserveBytes& need, hipStream_t main) {
   sf_status st = grow_device(r, &r->workspace, &r->workspace_bytes, need.device, main);
   if (st != SF_OK) return st;
   const uint64_t slot = need.slot;
@@ -529,4 +525,27 @@ extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, u
   if (r->arena && hipHostFree(r->arena) != hipSuccess) st = SF_ERR_HIP;
   r->arena = ptr;
   return st;
+}
+
+}  // namespace
+
+extern "C" sf_status sf_runner_reserve(sf_runner* r, uint64_t workspace_bytes, uint64_t work_bytes,
+                                       int32_t max_num_seqs, void* stream) {
+  if (!r || max_num_seqs < 0) return SF_ERR_INVALID_ARG;
+  // A smaller batch, or a step of another kind, may be planned in another way
+  // than the batch reserved for and take more than it.
+  return reserve(r, sf::reserve_bytes(&r->shape, &r->opts, workspace_bytes, work_bytes, max_num_seqs, -1),
+                 static_cast<hipStream_t>(stream));
+}
+
+extern "C" sf_status sf_runner_reserve_batch(sf_runner* r, const int32_t* seq_lens_host, int32_t num_seqs, void* stream) {
+  if (!r || num_seqs < 0 || (num_seqs > 0 && !seq_lens_host)) return SF_ERR_INVALID_ARG;
+  int64_t pages = 0;
+  for (int32_t s = 0; s < num_seqs; ++s) {
+    if (seq_lens_host[s] < 0) return SF_ERR_INVALID_ARG;
+    pages += (int64_t(seq_lens_host[s]) + sf::kPage - 1) / sf::kPage;
+  }
+  // Room for the batch to grow: the bounds stop at the planner's workers soon.
+  return reserve(r, sf::reserve_bytes(&r->shape, &r->opts, 0, 0, num_seqs, 2 * (pages + num_seqs) * r->shape.num_kv_heads),
+                 static_cast<hipStream_t>(stream));
 }

@@ -36,12 +36,13 @@ sf_status decode_plan_runner(const sf_attn_desc* desc, const int32_t* seq_lens_h
                              int32_t* work_host, uint64_t work_capacity_bytes, sf_plan_info* info);
 // What sf_runner_reserve takes: device memory (workspace and device copies of
 // rows) and a ring slot, for the plan that the caller names and for any plan
-// that decode_plan_runner makes for at most num_seqs sequences, of every kind.
+// that decode_plan_runner makes for at most num_seqs sequences and total_pages
+// pages of all their pairs (< 0: any number), of every kind.
 struct ReserveBytes {
   uint64_t device, slot;
 };
 ReserveBytes reserve_bytes(const sf_attn_desc* shape, const sf_plan_opts* opts, uint64_t workspace_bytes,
-                           uint64_t work_bytes, int32_t num_seqs);
+                           uint64_t work_bytes, int32_t num_seqs, int64_t total_pages);
 inline int64_t table_rows(int64_t workers) { return workers; }   // worker-table rows of a plan
 uint64_t desc_key(const sf_attn_desc* d);
 uint64_t align256(uint64_t x);

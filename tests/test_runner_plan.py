@@ -185,9 +185,13 @@ def test_shared_groups_are_the_runners_alone():
 def reserved(full, hq, hkv, d, kind, seqs, **opts):
     """Bytes (device, slot) that a reserve for the batch `full`, planned as a step of `kind`, sees to."""
     desc, info, _ = runner_plan(full, hq, hkv, d, kind, **opts)
+    return room_for(desc, info.workspace_bytes, info.work_bytes, seqs, -1, **opts)
+
+
+def room_for(desc, workspace, work, seqs, pages, **opts):
     got = np.zeros(2, np.uint64)
-    assert B.lib().sf_debug_runner_reserve(ctypes.byref(desc), ctypes.byref(B.make_opts(**opts)), info.workspace_bytes,
-                                           info.work_bytes, seqs, got.ctypes.data) == 0
+    assert B.lib().sf_debug_runner_reserve(ctypes.byref(desc), ctypes.byref(B.make_opts(**opts)), workspace, work, seqs, pages,
+                                           got.ctypes.data) == 0
     return got.tolist()
 
 
@@ -213,8 +217,13 @@ def test_smaller_batches_and_other_kinds_fit_what_a_large_one_reserves():
                int(rng.choice([40, 600, 4000, 20000]))) for _ in range(150)] + [(200, 4, 600)] * 60
     for trial, (n, hkv, top) in enumerate(trials):
         full = rng.integers(1, top, n)
-        opts = {} if trial % 5 else dict(workers_per_cu=int(rng.integers(1, 9)))
-        room = np.array([reserved(full, 4 * hkv, hkv, 128, kind, n, **opts) for kind in range(3)]).min(0)
+        opts = {} if trial % 4 else [dict(workers_per_cu=int(rng.integers(1, 9))), dict(chunk_pages=int(rng.integers(1, 200))),
+                                     dict(min_chunk_pages=int(rng.integers(1, 40))), dict(xcd_parity_skew=30)][trial // 4 % 4]
+        # by the lengths, and by the plan of any kind (a forced slice size has no bound without the lengths)
+        room = np.array([room_for(B.make_desc(0, 4 * hkv, hkv, 128, 1, 0, 1.0), 0, 0, n, int((-(-full // 16)).sum()) * hkv, **opts)])
+        if "chunk_pages" not in opts:
+            room = np.vstack([room, [reserved(full, 4 * hkv, hkv, 128, kind, n, **opts) for kind in range(3)]])
+        room = room.min(0)
         for part in range(4):
             lens = full
             if part:
@@ -228,8 +237,8 @@ def test_smaller_batches_and_other_kinds_fit_what_a_large_one_reserves():
 
 def test_reserve_is_bounded_for_any_options():
     """Worker counts beyond any batch's need do not become memory."""
-    desc, got = B.make_desc(0, 28, 4, 128, 1, 0, 1.0), np.zeros(2, np.uint64)
+    desc = B.make_desc(0, 28, 4, 128, 1, 0, 1.0)
     for opts in (dict(workers_per_cu=2**20), dict(num_cus=2**30), dict(num_cus=2**30, workers_per_cu=2**30), dict(chunk_pages=1)):
-        assert B.lib().sf_debug_runner_reserve(ctypes.byref(desc), ctypes.byref(B.make_opts(**opts)), 1000, 4096, 64,
-                                               got.ctypes.data) == 0
-        assert got.tolist() == [1024 + 4096 + 256, 12288]
+        assert room_for(desc, 1000, 4096, 64, -1, **opts) == [1024 + 4096 + 256, 12288]
+    # four short sequences of one KV head: a page of pinned memory per slot or two
+    assert room_for(B.make_desc(0, 4, 1, 64, 1, 0, 1.0), 0, 0, 4, 38)[1] <= 16384
