@@ -365,3 +365,25 @@ def test_object_dropped_during_a_capture():
     graph.replay()
     torch.cuda.synchronize()
     assert torch.equal(out, want) and torch.equal(B.ExtendAttention(8, 2, 64)(*args), want) and not B._scratch._dead
+
+
+def test_memory_taken_for_another_stream_is_waited_for():
+    """What an object lends is ordered on the current stream: before a first call
+    on another one, and before one that grows it, the current stream is waited for."""
+    side, waited = torch.cuda.Stream(), []
+    for lens, qls in (([60], [60]), ([8000] * 4, [256] * 4)):
+        eb = build_extend(lens, qls, 28, 4, 128, seed=3)
+        b = eb.batch
+        args = (eb.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.block_table).cuda(), b.seq_lens, eb.q_lens,
+                b.scale)
+        want = B.ExtendAttention(28, 4, 128)(*args)
+        torch.cuda.synchronize()
+        call = B.ExtendAttention(28, 4, 128)
+        lend = call._lend
+        call._lend = lambda slot, device, stream: (waited.append(stream), lend(slot, device, stream))
+        out = torch.empty_like(want)
+        torch.cuda.synchronize()
+        call(*args, out=out, stream=side)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    assert len(waited) == 3 and all(s is side for s in waited)
